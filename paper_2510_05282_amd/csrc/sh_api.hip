@@ -167,17 +167,15 @@ int projectors_noalloc(int lmax, int n_atoms, const TIO* centers, const int64_t*
     float2* pairs_f32 = reinterpret_cast<float2*>(base + kNoAllocPairs);
     double* coef = reinterpret_cast<double*>(base + kNoAllocPairs + kNoAllocPairsF32);
     const int ch = lmax + 1;
-    const int64_t nval = int64_t(n_tables) * ch * n_r;
     const double h = r_max / double(n_r - 1);
-    // every entry the solve reads it writes first, so the buffer needs no clearing
-    hipError_t e = shk::launch_spline_setup(values, pairs, coef, n_tables * ch, ch, n_r, h, stream);
+    // every entry the solve reads it writes first, so the buffer needs no clearing;
+    // only the pairs that the build reads are kept
+    constexpr bool f64 = sizeof(TIO) == 8;
+    const hipError_t e = shk::launch_spline_setup(values, f64 ? pairs : nullptr, f64 ? nullptr : pairs_f32, pairs,
+                                                  coef, n_tables * ch, ch, n_r, h, stream);
     const shk::knot_t<TIO>* table;
-    if constexpr (sizeof(TIO) == 8) {
-        table = pairs;
-    } else {
-        if (e == hipSuccess) e = shk::launch_narrow_tables(pairs, pairs_f32, nval, stream);
-        table = pairs_f32;
-    }
+    if constexpr (f64) table = pairs;
+    else table = pairs_f32;
     if (e != hipSuccess) return hip_status(e);
     shk::ProjArgs<TIO> A{centers, offsets, n_atoms, points, n_points, table, ch, n_tables, table_of_atom, n_r, h,
                          r_max, out};
@@ -378,8 +376,8 @@ int sh_radial_create(int lmax, int n_tables, int n_r, double r_max, const double
         hipError_t e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
         if (e == hipSuccess) e = hipMemcpyAsync(y, host_values, sizeof(double) * nval, hipMemcpyHostToDevice, st);
         if (e == hipSuccess)
-            e = shk::launch_spline_setup(y, h->table, scratch, int(n_ch), lmax + 1, n_r, h->h, st);
-        if (e == hipSuccess) e = shk::launch_narrow_tables(h->table, h->table_f32, nval, st);
+            e = shk::launch_spline_setup(y, h->table, h->table_f32, nullptr, scratch, int(n_ch), lmax + 1, n_r, h->h,
+                                         st);
         // the compact copies: the first L + 1 pairs of every knot row
         for (int L = 0; e == hipSuccess && L < n_compact; ++L) {
             e = shk::launch_compact_tables(h->table, h->compact[L], int64_t(rows), lmax + 1, L + 1, st);

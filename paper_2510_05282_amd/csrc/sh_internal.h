@@ -76,18 +76,17 @@ struct ProjArgs {
 template <typename TIO>
 hipError_t launch_projectors(int lmax, const ProjArgs<TIO>& A, hipStream_t s);
 
-// table_f32[k] = table[k] rounded to float, k < n (device arrays).
-hipError_t launch_narrow_tables(const double2* table, float2* table_f32, int64_t n, hipStream_t s);
-
 // The first ch_out pairs of each of `rows` rows of ch_in pairs: out[rows][ch_out]
 // from in[rows][ch_in] (device arrays, P = double2 or float2, 1 <= ch_out <= ch_in).
 template <typename P>
 hipError_t launch_compact_tables(const P* in, P* out, int64_t rows, int ch_in, int ch_out, hipStream_t s);
 
 // Natural-spline second derivatives for n_ch = n_tables * ch channels of n_r
-// values y[n_ch][n_r] (device): writes (y, M) pairs to table[n_tables][n_r][ch];
-// scratch holds n_ch * n_r doubles.
-hipError_t launch_spline_setup(const double* y, double2* table, double* scratch, int n_ch, int ch, int n_r,
-                               double h, hipStream_t s);
+// values y[n_ch][n_r] (device): writes (y, M) pairs to table[n_tables][n_r][ch] and,
+// rounded to float, to table_f32 of the same layout (either may be null; work, of the
+// same size as table, is scratch that must be given when table is null); scratch holds
+// n_ch * n_r doubles.
+hipError_t launch_spline_setup(const double* y, double2* table, float2* table_f32, double2* work, double* scratch,
+                               int n_ch, int ch, int n_r, double h, hipStream_t s);
 
 }  // namespace shk

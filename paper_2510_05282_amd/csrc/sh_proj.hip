@@ -30,15 +30,206 @@ namespace shk {
 
 // ---------------------------------------------------------------- spline set-up
 
-// One thread per channel c = (table t = c / ch, channel l = c % ch): values
-// y[c][n_r] in, pairs to table[t][k][l] (spline_solve), scratch cp[c][n_r].
-__global__ void spline_setup_kernel(const double* __restrict__ y, double2* __restrict__ table,
-                                    double* __restrict__ cp, int n_ch, int ch, int n_r, double six_over_h2)
+// The eliminated super-diagonal c_k = 1 / (4 - c_{k-1}), c_0 = 0, of spline_solve: the
+// same for every channel, and from k = kSplineCs - 1 on a fixed point in double
+// (c -> 1 / (4 - c) contracts by 0.07 near 2 - sqrt(3)).
+constexpr int kSplineCs = 24;
+struct SplineC {
+    double c[kSplineCs];
+    constexpr SplineC() : c{}
+    {
+        for (int k = 1; k < kSplineCs; ++k) c[k] = 1.0 / (4.0 - c[k - 1]);
+    }
+};
+constexpr SplineC kSplineC;
+static_assert(1.0 / (4.0 - kSplineC.c[kSplineCs - 1]) == kSplineC.c[kSplineCs - 1], "c_k has not settled");
+__device__ constexpr SplineC kSplineCDev;
+
+__device__ __forceinline__ double spline_c(int k)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    constexpr double last = kSplineC.c[kSplineCs - 1];
+    return k < kSplineCs ? kSplineCDev.c[k] : last;
+}
+
+constexpr int kSplineBlock = 256;                        // threads per channel
+constexpr int kSplinePer = 8;                            // adjacent knots per thread
+constexpr int kSplineTile = kSplineBlock * kSplinePer;   // knots per pass of a workgroup
+// LDS slot of knot j of a tile: one slot of padding per kSplinePer, so that lanes
+// reading kSplinePer knots apart spread over the banks.
+__device__ __forceinline__ constexpr int spline_slot(int j) { return j + j / kSplinePer; }
+
+// Composition of affine maps v -> a v + b over the workgroup: on entry each thread's
+// own map, on return the map of all threads before it (REV: after it), in their order
+// of application.  Every thread must call it; tot holds one map per wave.
+struct Affine {
+    double a, b;
+};
+template <bool REV>
+__device__ __forceinline__ Affine block_before(Affine own, Affine* tot)
+{
+    const int wl = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int s = 1; s < 64; s *= 2) {
+        const double a = REV ? __shfl_down(own.a, s) : __shfl_up(own.a, s);
+        const double b = REV ? __shfl_down(own.b, s) : __shfl_up(own.b, s);
+        if (REV ? wl + s < 64 : wl >= s) {
+            own.b = own.a * b + own.b;
+            own.a = own.a * a;
+        }
+    }
+    if (wl == (REV ? 0 : 63)) tot[wave] = own;
+    Affine m{REV ? __shfl_down(own.a, 1) : __shfl_up(own.a, 1), REV ? __shfl_down(own.b, 1) : __shfl_up(own.b, 1)};
+    if (wl == (REV ? 63 : 0)) m = Affine{1.0, 0.0};
+    __syncthreads();
+    constexpr int kWaves = kSplineBlock / 64;
+#pragma unroll
+    for (int q = 1; q < kWaves; ++q) {  // the waves before this one, nearest first
+        const int w = REV ? wave + q : wave - q;
+        if (w >= 0 && w < kWaves) {
+            m.b = m.a * tot[w].b + m.b;
+            m.a = m.a * tot[w].a;
+        }
+    }
+    __syncthreads();
+    return m;
+}
+
+// One workgroup per channel c = (table t = c / ch, channel l = c % ch): values y[c][n_r]
+// in, pairs to table[t][k][l] and, rounded to float, to table_f32 (each if not null).
+// The tridiagonal solve of spline_solve is a chain of n_r dependent steps each way,
+//     d_k = (rhs_k - d_{k-1}) / (4 - c_{k-1}),   M_k = d_k - c_k M_{k+1},
+// but every step is an affine map of the one before with |slope| < 0.27 and c_k is known
+// beforehand, so each thread composes the maps of its kSplinePer knots, a scan over the
+// workgroup gives the value its first knot starts from, and it then takes its own steps
+// from there.  Channels longer than kSplineTile take several passes each way, carrying
+// one value from pass to pass and d in cp[c][n_r].  Where a right-hand side is not finite
+// (a value of y that is not) or near overflow, one thread runs spline_solve, so that
+// infinities and NaN spread as there; `work` is where its pairs go when table is null.
+// Bound by latency: with one thread per channel 168 channels of 2000 knots took 1.48 ms
+// (0.74 us per knot, 168 lanes of the GPU busy); this takes 8 us.
+__global__ __launch_bounds__(kSplineBlock) void spline_setup_kernel(const double* __restrict__ y,
+                                                                    double2* __restrict__ table,
+                                                                    float2* __restrict__ table_f32,
+                                                                    double2* __restrict__ work,
+                                                                    double* __restrict__ cp, int64_t c0, int ch,
+                                                                    int n_r, double six_over_h2)
+{
+    __shared__ double ys[spline_slot(kSplineTile + 2) + 1], ms[spline_slot(kSplineTile) + 1];
+    __shared__ Affine tot[kSplineBlock / 64];
+    __shared__ double edge;
+    const int tid = threadIdx.x;
+    // the channels of a table on one XCD, whose L2 then merges the lines they share
+    const int64_t c = c0 + xcd_tile(blockIdx.x, gridDim.x);
+    const double* yc = y + c * n_r;
+    double* dc = cp + c * n_r;
+    const int64_t at0 = c / ch * n_r * ch + c % ch;
+    const int nt = (n_r + kSplineTile - 1) / kSplineTile;
+    auto interior = [&](int k) { return k >= 1 && k <= n_r - 2; };
+    double d[kSplinePer];
+    double carry = 0.0;
+    for (int t = 0; t < nt; ++t) {
+        const int base = t * kSplineTile;
+        for (int j = tid; j < kSplineTile + 2; j += kSplineBlock) {  // slot j holds y[base - 1 + j]
+            const int k = base - 1 + j;
+            ys[spline_slot(j)] = k >= 0 && k < n_r ? yc[k] : 0.0;
+        }
+        __syncthreads();
+        const int k0 = base + tid * kSplinePer;
+        bool bad = false;
+        Affine own{1.0, 0.0};
+#pragma unroll
+        for (int i = 0; i < kSplinePer; ++i) {
+            const int j = tid * kSplinePer + i;
+            const double rhs = six_over_h2 * (ys[spline_slot(j + 2)] - 2.0 * ys[spline_slot(j + 1)] + ys[spline_slot(j)]);
+            d[i] = rhs;
+            if (interior(k0 + i)) {
+                const double ck = spline_c(k0 + i);
+                own.b = (rhs - own.b) * ck;
+                own.a = -own.a * ck;
+                bad = bad || !(fabs(rhs) < 0x1p+1000);
+            } else {
+                own = Affine{0.0, 0.0};
+            }
+        }
+        if (__syncthreads_or(bad)) {
+            double2* tc = (table ? table : work) + at0;
+            if (tid == 0) spline_solve(yc, tc, ch, dc, n_r, six_over_h2);
+            __syncthreads();
+            if (table_f32)
+                for (int k = tid; k < n_r; k += kSplineBlock) {
+                    const double2 v = tc[int64_t(k) * ch];
+                    table_f32[at0 + int64_t(k) * ch] = make_float2(float(v.x), float(v.y));
+                }
+            return;
+        }
+        const Affine m = block_before<false>(own, tot);
+        double v = m.a * carry + m.b;
+#pragma unroll
+        for (int i = 0; i < kSplinePer; ++i) {
+            if (interior(k0 + i)) {
+                // (rhs - v) / (4 - c_{k-1}) through the reciprocal c_k and one correction
+                const double ck = spline_c(k0 + i), x = d[i] - v, den = 4.0 - spline_c(k0 + i - 1), q = x * ck;
+                v = __builtin_fma(__builtin_fma(-q, den, x), ck, q);
+            } else {
+                v = 0.0;
+            }
+            d[i] = v;
+            if (nt > 1 && k0 + i < n_r) dc[k0 + i] = v;
+        }
+        if (tid == kSplineBlock - 1) edge = v;
+        __syncthreads();
+        carry = edge;
+    }
+    carry = 0.0;
+    for (int t = nt - 1; t >= 0; --t) {
+        const int base = t * kSplineTile, k0 = base + tid * kSplinePer;
+        Affine own{1.0, 0.0};
+#pragma unroll
+        for (int i = kSplinePer - 1; i >= 0; --i) {
+            if (nt > 1) d[i] = k0 + i < n_r ? dc[k0 + i] : 0.0;
+            if (interior(k0 + i)) {
+                const double ck = spline_c(k0 + i);
+                own.b = d[i] - ck * own.b;
+                own.a = -ck * own.a;
+            } else {
+                own = Affine{0.0, 0.0};
+            }
+        }
+        const Affine m = block_before<true>(own, tot);
+        double v = m.a * carry + m.b;
+#pragma unroll
+        for (int i = kSplinePer - 1; i >= 0; --i) {
+            v = interior(k0 + i) ? d[i] - spline_c(k0 + i) * v : 0.0;
+            ms[spline_slot(tid * kSplinePer + i)] = v;
+        }
+        if (tid == 0) edge = v;
+        __syncthreads();
+        carry = edge;
+        for (int j = tid; j < kSplineTile && base + j < n_r; j += kSplineBlock) {
+            const double2 p = make_double2(nt > 1 ? yc[base + j] : ys[spline_slot(j + 1)], ms[spline_slot(j)]);
+            const int64_t at = at0 + int64_t(base + j) * ch;
+            if (table) table[at] = p;
+            if (table_f32) table_f32[at] = make_float2(float(p.x), float(p.y));
+        }
+        __syncthreads();
+    }
+}
+
+// The same with one thread per channel, for many short channels (launch_spline_setup).
+__global__ __launch_bounds__(64) void spline_serial_kernel(const double* __restrict__ y, double2* __restrict__ table,
+                                                           float2* __restrict__ table_f32,
+                                                           double2* __restrict__ work, double* __restrict__ cp,
+                                                           int64_t c0, int64_t n_ch, int ch, int n_r,
+                                                           double six_over_h2)
+{
+    const int64_t c = c0 + int64_t(blockIdx.x) * 64 + threadIdx.x;
     if (c >= n_ch) return;
-    spline_solve(y + int64_t(c) * n_r, table + int64_t(c / ch) * n_r * ch + c % ch, ch, cp + int64_t(c) * n_r, n_r,
-                 six_over_h2);
+    const int64_t at0 = c / ch * n_r * ch + c % ch;
+    double2* tc = (table ? table : work) + at0;
+    spline_solve(y + c * n_r, tc, ch, cp + c * n_r, n_r, six_over_h2);
+    if (table_f32)
+        for (int64_t k = 0; k < n_r; ++k)
+            table_f32[at0 + k * ch] = make_float2(float(tc[k * ch].x), float(tc[k * ch].y));
 }
 
 // Flat projector kernel over the concatenated atom point sets, PPL adjacent
@@ -331,19 +522,6 @@ hipError_t launch_projectors(int lmax, const ProjArgs<TIO>& A, hipStream_t s)
 template hipError_t launch_projectors<double>(int, const ProjArgs<double>&, hipStream_t);
 template hipError_t launch_projectors<float>(int, const ProjArgs<float>&, hipStream_t);
 
-__global__ void narrow_tables_kernel(const double2* __restrict__ in, float2* __restrict__ out, int64_t n)
-{
-    const int64_t k = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (k < n) out[k] = make_float2(float(in[k].x), float(in[k].y));
-}
-
-hipError_t launch_narrow_tables(const double2* table, float2* table_f32, int64_t n, hipStream_t s)
-{
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(narrow_tables_kernel, dim3(unsigned((n + 255) / 256)), dim3(256), 0, s, table, table_f32, n);
-    return hipGetLastError();
-}
-
 // out[row][c] = in[row][c] for c < ch_out (rows of ch_in pairs in, ch_out out)
 template <typename P>
 __global__ void compact_tables_kernel(const P* __restrict__ in, P* __restrict__ out, int64_t rows, int ch_in,
@@ -369,13 +547,29 @@ hipError_t launch_compact_tables(const P* in, P* out, int64_t rows, int ch_in, i
 template hipError_t launch_compact_tables<double2>(const double2*, double2*, int64_t, int, int, hipStream_t);
 template hipError_t launch_compact_tables<float2>(const float2*, float2*, int64_t, int, int, hipStream_t);
 
-hipError_t launch_spline_setup(const double* y, double2* table, double* scratch, int n_ch, int ch, int n_r,
-                               double h, hipStream_t s)
+hipError_t launch_spline_setup(const double* y, double2* table, float2* table_f32, double2* work, double* scratch,
+                               int n_ch, int ch, int n_r, double h, hipStream_t s)
 {
-    const int block = 64;
-    hipLaunchKernelGGL(spline_setup_kernel, dim3((n_ch + block - 1) / block), dim3(block), 0, s, y, table,
-                       scratch, n_ch, ch, n_r, 6.0 / (h * h));
-    return hipGetLastError();
+    // a dispatch counts its work-items in 32 bits
+    constexpr int64_t kChunk = int64_t(1) << 22;
+    // A workgroup per channel costs 8.5 us per 1000 channels whatever their length up to
+    // kSplineTile, a thread per channel about 0.75 us per knot until the lanes fill the GPU.
+    // Measured, thread against workgroup per channel, with a one-tile build after it:
+    // 260000 x 8 knots 50 / 1874 us, 10000 x 64 55 / 90, 16000 x 128 104 / 148, 1000 x 16
+    // 18 / 17, 8000 x 256 202 / 84, 168 x 300 190 / 17, 168 x 2000 1390 / 18.
+    const bool serial = n_ch > int64_t(96) * n_r;
+    for (int64_t c0 = 0; c0 < n_ch; c0 += kChunk) {
+        const int64_t nc = n_ch - c0 < kChunk ? n_ch - c0 : kChunk;
+        if (serial)
+            hipLaunchKernelGGL(spline_serial_kernel, dim3(unsigned((nc + 63) / 64)), dim3(64), 0, s, y, table,
+                               table_f32, work, scratch, c0, int64_t(n_ch), ch, n_r, 6.0 / (h * h));
+        else
+            hipLaunchKernelGGL(spline_setup_kernel, dim3(unsigned(nc)), dim3(kSplineBlock), 0, s, y, table, table_f32,
+                               work, scratch, c0, ch, n_r, 6.0 / (h * h));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace shk
