@@ -5,20 +5,16 @@
 // path moves 3s + F s bytes per point (s = element size) against a few hundred
 // flops, so it is bound by HBM stores.  Launch choices, all measured on MI355X:
 //  - Each lane evaluates 16 bytes' worth of adjacent points (two in FP64, four
-//    in FP32) and stores 16 bytes per row: one contiguous 1 KiB run per wave and
-//    row.  Outputs whose rows are not 16-byte aligned take the one-point kernel,
-//    and so do calls of fewer than kFwdVecPoints points: a launch that leaves CUs
-//    idle lasts as long as one workgroup's chain of work, which the wider lanes
-//    lengthen (kernel trace, lmax 9, 4k / 16k / 64k / 100k points: FP64 5.4 / 6.8 /
-//    10.1 / 14.0 us with one point per lane against 6.6 / 8.1 / 10.6 / 14.1 with
-//    two, FP32 4.2 / 4.8 / 7.1 / 9.1 against 7.6 / 8.4 / 10.0 / 10.4 with four;
-//    equal at 2^18 points, the wide lanes ahead above).
+//    in FP32) and stores 16 bytes per row, at any element alignment: one contiguous
+//    1 KiB run per wave and row.  Outputs below kFwdVecBytes take one point per lane:
+//    they stay in the caches on the way out, and what such a launch lasts is its
+//    workgroups' chain of work, which the wider lanes lengthen.
 //  - Workgroups are remapped so each XCD walks one contiguous range of points.
-//  - The 16-byte kernels reserve LDS they do not use, which caps the resident
-//    workgroups per CU at 2 (8 waves).  Fewer points in flight keep the
-//    concurrent writes of each row in a smaller window, which the HBM write path
-//    turns into 3-14% more bandwidth depending on lmax; the one-point kernel
-//    runs uncapped (with 4-byte stores it needs the extra waves).
+//  - The kernels of large outputs reserve LDS they do not use, which caps the
+//    resident workgroups per CU.  Fewer points in flight keep the concurrent writes of
+//    each row in a smaller window, which the HBM write path rewards, and most where
+//    the rows are not 16-byte aligned: there neighbouring waves write parts of the
+//    same lines, which merge in the L2 only while both are at work (fwd_shape).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -31,20 +27,45 @@ namespace shk {
 // the store address is a scalar row base plus a 32-bit per-lane offset.
 constexpr int64_t kChunk = int64_t(1) << 28;
 
-// Calls of at least this many points take the 16-byte lanes.
+// Calls of at least this many points take the 16-byte lanes (complex and spinor).
 constexpr int64_t kFwdVecPoints = int64_t(1) << 18;
 
-// LDS reserved (not used) per 256-thread workgroup of the 16-byte kernels: more
-// than a third of the CU's 160 KiB, so at most 2 workgroups are resident per CU.
-constexpr size_t kCapLds = 54 * 1024;
+// LDS reserved (not used) per 256-thread workgroup, of the CU's 160 KiB: at most 3, 2
+// or 1 resident workgroups per CU.
+constexpr size_t kCapLds3 = 40 * 1024, kCapLds = 54 * 1024, kCapLds1 = 84 * 1024;
 
-// The same for the real-harmonic kernel: FP64 at lmax >= 8 reserves more than half
-// of the LDS, one resident workgroup (4 waves) per CU, fewer row streams at once.
-// Measured on 2^26 points, fractions of 8 TB/s over five runs: FP64 lmax 9 67.8% ->
-// 68.1-68.4%, lmax 8 68.0% -> 68.1-68.2%; lmax 7 and below and FP32 at every lmax
-// equal or slower (FP64 lmax 2 74 -> 70%, FP32 lmax 2 74 -> 63%).
-template <typename TIO, int LMAX>
-constexpr size_t kFwdCapLds = sizeof(TIO) == 8 && LMAX >= 8 ? 84 * 1024 : kCapLds;
+// Lanes and LDS reservation of the real harmonics' launch, from the bytes it writes and
+// the alignment of its rows.  Measured in us, 3 inputs and outputs in turn, as points per
+// lane / KiB reserved (even n, then odd n):
+//  below 2^27 bytes  1/0: FP64 lmax 6, 2^18 points (103 MB) 18.6 against 19.0 with 2/54;
+//                    FP32 lmax 3, 2^20 (67 MB) 12.7 against 13.5 with 4/54, lmax 9, 2^17
+//                    9.7 against 10.8; odd n the same, but within 4% of 2^27.
+//  lmax 1            one point: 2^25 points FP64 1/40 307, 1/0 328, 2/54 321; FP32 1/0
+//                    156, 4/54 184 (two or four rows' worth of work per point is too
+//                    little to spread over wide lanes)
+//  lmax 0            2^25 points FP32 4/0 22.1, 4/54 22.8, 1/0 32.0; FP64 equal
+//  lmax 2            2^25 points FP64 2/54 563, 2/0 608, 2/84 582; FP32 4/54 283, 4/84 324
+//  lmax >= 3         one resident workgroup: FP64 lmax 3, 2^25 points 2/84 875, 2/54 910;
+//                    lmax 9, 2^22 2/84 647, 2/54 642; odd n 2/84 661, 2/54 748, 2/0 783,
+//                    1/0 857; FP32 lmax 8, 2^23 4/84 521, 4/54 522; odd n 532, 594, 1/0 820
+//  the same, aligned rows below 2^30 bytes: uncapped, FP64 lmax 9, 2^20 2/0 158.6, 2/84
+//                    162.4; FP32 lmax 5, 2^21 4/0 61.3, 4/84 63.6
+constexpr int64_t kFwdVecBytes = int64_t(1) << 27, kFwdCapBytes = int64_t(1) << 30;
+
+struct FwdShape {
+    bool wide;  // 16 bytes of points per lane, else one point
+    size_t lds;
+};
+template <int LMAX, typename TIO>
+static FwdShape fwd_shape(int64_t n, bool aligned)
+{
+    const int64_t bytes = n * nfun(LMAX) * int64_t(sizeof(TIO));
+    if (bytes < kFwdVecBytes) return {false, 0};
+    if (LMAX == 0) return {true, 0};
+    if (LMAX == 1) return {false, sizeof(TIO) == 8 ? kCapLds3 : 0};
+    if (LMAX == 2) return {true, kCapLds};
+    return {true, aligned && bytes < kFwdCapBytes ? 0 : kCapLds1};
+}
 
 // Input pointers of a launch that starts at point c0.
 template <In MODE, typename TIO>
@@ -59,11 +80,10 @@ struct Inputs {
 };
 
 template <int LMAX, typename TIO, int PPL, In MODE>
-static hipError_t launch_one(Inputs<MODE, TIO> in, TIO* out, int64_t n, int64_t ld, hipStream_t s)
+static hipError_t launch_one(Inputs<MODE, TIO> in, TIO* out, int64_t n, int64_t ld, hipStream_t s, size_t lds)
 {
-    const int64_t nvec = n / PPL;
+    const int64_t nvec = (n + PPL - 1) / PPL;
     const unsigned grid = unsigned((nvec + kFwdBlock - 1) / kFwdBlock);
-    constexpr size_t lds = PPL > 1 ? kFwdCapLds<TIO, LMAX> : 0;
     hipLaunchKernelGGL((fwd_kernel<LMAX, TIO, PPL, MODE>), dim3(grid), dim3(kFwdBlock), lds, s,
                        in.a, out, uint32_t(n), ld, in.b);
     return hipGetLastError();
@@ -72,20 +92,13 @@ static hipError_t launch_one(Inputs<MODE, TIO> in, TIO* out, int64_t n, int64_t 
 template <int LMAX, typename TIO, In MODE>
 static hipError_t launch_fwd_l(int64_t n, Inputs<MODE, TIO> in, TIO* out, int64_t ld, hipStream_t s)
 {
-    constexpr int kVec = 16 / sizeof(TIO);
-    const bool vec_ok = n >= kFwdVecPoints && ld % kVec == 0 &&
-                        reinterpret_cast<uintptr_t>(out) % (kVec * sizeof(TIO)) == 0;
+    constexpr int kVec = LMAX == 1 ? 1 : 16 / sizeof(TIO);  // fwd_shape never asks lmax 1 for more
+    const FwdShape f = fwd_shape<LMAX, TIO>(n, ld * sizeof(TIO) % 16 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0);
     for (int64_t c0 = 0; c0 < n; c0 += kChunk) {
         const int64_t nc = n - c0 < kChunk ? n - c0 : kChunk;
-        hipError_t e;
-        if (vec_ok) {
-            const int64_t nmain = nc - nc % kVec;
-            e = nmain ? launch_one<LMAX, TIO, kVec, MODE>(in.at(c0), out + c0, nmain, ld, s) : hipSuccess;
-            if (e == hipSuccess && nmain < nc)
-                e = launch_one<LMAX, TIO, 1, MODE>(in.at(c0 + nmain), out + c0 + nmain, nc - nmain, ld, s);
-        } else {
-            e = launch_one<LMAX, TIO, 1, MODE>(in.at(c0), out + c0, nc, ld, s);
-        }
+        const hipError_t e = f.wide && nc >= kVec
+                                 ? launch_one<LMAX, TIO, kVec, MODE>(in.at(c0), out + c0, nc, ld, s, f.lds)
+                                 : launch_one<LMAX, TIO, 1, MODE>(in.at(c0), out + c0, nc, ld, s, f.lds);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

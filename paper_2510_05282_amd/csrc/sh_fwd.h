@@ -24,6 +24,11 @@ constexpr int kFwdBlock = 256;
 template <typename S, int N> struct vec_of { typedef S type __attribute__((ext_vector_type(N))); };
 template <typename S> struct vec_of<S, 1> { typedef S type; };
 
+// The same aligned only as its elements: a 16-byte access of it is one instruction at any
+// element address.
+template <typename S, int N> struct uvec_of { typedef S type __attribute__((ext_vector_type(N), aligned(sizeof(S)))); };
+template <typename S> struct uvec_of<S, 1> { typedef S type; };
+
 template <typename V, int PPL>
 __device__ __forceinline__ auto& lane(V& v, int k)
 {
@@ -63,8 +68,9 @@ __device__ __forceinline__ void load_unit(const TIO* __restrict__ a, const TIO* 
 // out is [F][ld]; the input is xyz [n][3] (kXyz, kUnit) or theta = xyz[n],
 // phi = in1[n] (kAngles); n * sizeof(TIO) < 2^31 so per-row byte offsets
 // fit 32 bits (the host splits larger batches).  With PPL > 1 the host
-// guarantees n % PPL == 0, ld % PPL == 0 and a PPL * sizeof(TIO)-aligned out
-// (a remainder of fewer than PPL points goes to a PPL = 1 launch).
+// guarantees n >= PPL; ld and out need no alignment beyond the element's.  Where PPL
+// does not divide n the last lane takes the last PPL points, some of which the lane
+// before it takes too: both store the same bits.
 template <int LMAX, typename TIO, int PPL, In MODE = In::kXyz>
 __global__ __launch_bounds__(kFwdBlock) void fwd_kernel(const TIO* __restrict__ xyz, TIO* __restrict__ out,
                                                         uint32_t n, int64_t ld, const TIO* __restrict__ in1)
@@ -72,8 +78,8 @@ __global__ __launch_bounds__(kFwdBlock) void fwd_kernel(const TIO* __restrict__ 
     using V = typename vec_of<TIO, PPL>::type;
     const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
     const uint32_t t = b * kFwdBlock + threadIdx.x;  // vector index
-    const uint32_t i0 = t * PPL;                     // first point of this lane
-    if (i0 >= n) return;
+    if (t * PPL >= n) return;
+    const uint32_t i0 = t * PPL + PPL <= n ? t * PPL : n - PPL;  // first point of this lane
     V x, y, z, k;
 #pragma unroll
     for (int q = 0; q < PPL; ++q) {
@@ -86,7 +92,7 @@ __global__ __launch_bounds__(kFwdBlock) void fwd_kernel(const TIO* __restrict__ 
     }
     const uint32_t boff = i0 * uint32_t(sizeof(TIO));
     eval_unit<LMAX, V>(x, y, z, k, [&](int r, V v) {
-        *reinterpret_cast<V*>(reinterpret_cast<char*>(out + int64_t(r) * ld) + boff) = v;
+        *reinterpret_cast<typename uvec_of<TIO, PPL>::type*>(reinterpret_cast<char*>(out + int64_t(r) * ld) + boff) = v;
     });
 }
 

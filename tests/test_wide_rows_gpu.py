@@ -1,0 +1,68 @@
+"""Launches whose lanes take 16 bytes of points at any alignment of the output rows.
+
+Such a launch covers the points with whole vectors, the last of which overlaps its
+neighbour where the lane width does not divide n; it is chosen from the bytes it
+writes.  Its values are compared bit for bit with those of small calls over pieces of
+the same points (one point per lane), for n around the sizes where the choice changes
+and every remainder, with padded and misaligned outputs whose padding must stay
+untouched."""
+from __future__ import annotations
+
+import pytest
+import torch
+
+import paper_2510_05282_amd as sh
+
+pytestmark = pytest.mark.gpu
+DTYPES = [torch.float64, torch.float32]
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+def _points(n, dtype, dev, seed=0):
+    g = torch.Generator(device=dev)
+    g.manual_seed(seed)
+    x = torch.randn((n, 3), generator=g, dtype=torch.float64, device=dev)
+    x[n // 2] = 0.0  # the origin
+    x[n - 1] = torch.tensor([0.0, 0.0, -1e-9], dtype=torch.float64)
+    return x.to(dtype).contiguous()
+
+
+def _pieces(fn, x, piece):
+    return [(i, fn(x[i:i + piece].contiguous())) for i in range(0, x.shape[0], piece)]
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("lmax", [0, 1, 2, 3, 6, 9])
+@pytest.mark.parametrize("more", [-1, 0, 1, 2, 3])
+def test_real_rows(dev, dtype, lmax, more):
+    size, F = torch.finfo(dtype).bits // 8, (lmax + 1) ** 2
+    n = -(-(1 << 27) // (F * size)) // 4 * 4 + 4 + more  # about 2^27 bytes of output
+    print("case: wide rows, lmax", lmax, "n", n, dtype, flush=True)
+    x = _points(n, dtype, dev)
+    pad, head = 5, 1  # an odd row stride and a start off the 16-byte boundary
+    buf = torch.full((F * (n + pad) + head,), -7.0, dtype=dtype, device=dev)
+    out = buf[head:].view(F, n + pad)
+    sh.sh_eval_ld(lmax, x, out[:, :n])
+    y = (sh.sh_eval if dtype == torch.float64 else sh.sh_eval_f32)(lmax, x)
+    assert torch.equal(y, out[:, :n])
+    assert bool((out[:, n:] == -7.0).all()) and float(buf[0]) == -7.0
+    fn = sh.sh_eval if dtype == torch.float64 else sh.sh_eval_f32
+    for i, p in _pieces(lambda v: fn(lmax, v), x, n // 3 + 1):
+        assert torch.equal(y[:, i:i + p.shape[1]], p)
+
+
+def test_real_rows_above_the_cap_size(dev):
+    """2^30 bytes and more, aligned and not, where the launch reserves LDS."""
+    n = (1 << 30) // 800 + 5
+    print("case: wide rows above 2^30 bytes", flush=True)
+    for m in (n // 2 * 2, n // 2 * 2 + 1):
+        x = _points(m, torch.float64, dev, seed=m)
+        y = sh.sh_eval(9, x)
+        for i, p in _pieces(lambda v: sh.sh_eval(9, v), x, 150001):
+            assert torch.equal(y[:, i:i + p.shape[1]], p)
