@@ -13,8 +13,8 @@
 //  - The kernels of large outputs reserve LDS they do not use, which caps the
 //    resident workgroups per CU.  Fewer points in flight keep the concurrent writes of
 //    each row in a smaller window, which the HBM write path rewards, and most where
-//    the rows are not 16-byte aligned: there neighbouring waves write parts of the
-//    same lines, which merge in the L2 only while both are at work (fwd_shape).
+//    the rows do not start on cache lines: there neighbouring waves write parts of the
+//    same lines, which merge in the L2 only while both are at work (store_shape).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -26,46 +26,6 @@ namespace shk {
 // Points per launch: keeps every per-row byte offset of a launch below 2^31 so
 // the store address is a scalar row base plus a 32-bit per-lane offset.
 constexpr int64_t kChunk = int64_t(1) << 28;
-
-// Calls of at least this many points take the 16-byte lanes (complex and spinor).
-constexpr int64_t kFwdVecPoints = int64_t(1) << 18;
-
-// LDS reserved (not used) per 256-thread workgroup, of the CU's 160 KiB: at most 3, 2
-// or 1 resident workgroups per CU.
-constexpr size_t kCapLds3 = 40 * 1024, kCapLds = 54 * 1024, kCapLds1 = 84 * 1024;
-
-// Lanes and LDS reservation of the real harmonics' launch, from the bytes it writes and
-// the alignment of its rows.  Measured in us, 3 inputs and outputs in turn, as points per
-// lane / KiB reserved (even n, then odd n):
-//  below 2^27 bytes  1/0: FP64 lmax 6, 2^18 points (103 MB) 18.6 against 19.0 with 2/54;
-//                    FP32 lmax 3, 2^20 (67 MB) 12.7 against 13.5 with 4/54, lmax 9, 2^17
-//                    9.7 against 10.8; odd n the same, but within 4% of 2^27.
-//  lmax 1            one point: 2^25 points FP64 1/40 307, 1/0 328, 2/54 321; FP32 1/0
-//                    156, 4/54 184 (two or four rows' worth of work per point is too
-//                    little to spread over wide lanes)
-//  lmax 0            2^25 points FP32 4/0 22.1, 4/54 22.8, 1/0 32.0; FP64 equal
-//  lmax 2            2^25 points FP64 2/54 563, 2/0 608, 2/84 582; FP32 4/54 283, 4/84 324
-//  lmax >= 3         one resident workgroup: FP64 lmax 3, 2^25 points 2/84 875, 2/54 910;
-//                    lmax 9, 2^22 2/84 647, 2/54 642; odd n 2/84 661, 2/54 748, 2/0 783,
-//                    1/0 857; FP32 lmax 8, 2^23 4/84 521, 4/54 522; odd n 532, 594, 1/0 820
-//  the same, aligned rows below 2^30 bytes: uncapped, FP64 lmax 9, 2^20 2/0 158.6, 2/84
-//                    162.4; FP32 lmax 5, 2^21 4/0 61.3, 4/84 63.6
-constexpr int64_t kFwdVecBytes = int64_t(1) << 27, kFwdCapBytes = int64_t(1) << 30;
-
-struct FwdShape {
-    bool wide;  // 16 bytes of points per lane, else one point
-    size_t lds;
-};
-template <int LMAX, typename TIO>
-static FwdShape fwd_shape(int64_t n, bool aligned)
-{
-    const int64_t bytes = n * nfun(LMAX) * int64_t(sizeof(TIO));
-    if (bytes < kFwdVecBytes) return {false, 0};
-    if (LMAX == 0) return {true, 0};
-    if (LMAX == 1) return {false, sizeof(TIO) == 8 ? kCapLds3 : 0};
-    if (LMAX == 2) return {true, kCapLds};
-    return {true, aligned && bytes < kFwdCapBytes ? 0 : kCapLds1};
-}
 
 // Input pointers of a launch that starts at point c0.
 template <In MODE, typename TIO>
@@ -92,8 +52,9 @@ static hipError_t launch_one(Inputs<MODE, TIO> in, TIO* out, int64_t n, int64_t 
 template <int LMAX, typename TIO, In MODE>
 static hipError_t launch_fwd_l(int64_t n, Inputs<MODE, TIO> in, TIO* out, int64_t ld, hipStream_t s)
 {
-    constexpr int kVec = LMAX == 1 ? 1 : 16 / sizeof(TIO);  // fwd_shape never asks lmax 1 for more
-    const FwdShape f = fwd_shape<LMAX, TIO>(n, ld * sizeof(TIO) % 16 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0);
+    constexpr int kVec = LMAX == 1 ? 1 : 16 / sizeof(TIO);  // store_shape never asks lmax 1 for more
+    const StoreShape f = store_shape<nfun(LMAX), TIO>(n * nfun(LMAX) * int64_t(sizeof(TIO)),
+                                                      on_lines(out, ld * sizeof(TIO)));
     for (int64_t c0 = 0; c0 < n; c0 += kChunk) {
         const int64_t nc = n - c0 < kChunk ? n - c0 : kChunk;
         const hipError_t e = f.wide && nc >= kVec
@@ -141,10 +102,9 @@ hipError_t launch_fwd_angles(int lmax, int64_t n, const TIO* theta, const TIO* p
     return dispatch<TIO, In::kAngles>(lmax, n, {theta, phi}, out, ld, s);
 }
 
-// Complex and spinor kernels: 16 bytes per lane and row (one FP64 complex, or two
-// FP32 complex values of adjacent points), capped like the 16-byte real kernels.
-// FP32 outputs whose rows are not 16-byte aligned, and a last odd point, take
-// one point per lane.
+// Complex and spinor kernels: 16 bytes per lane and row (one FP64 complex, or two FP32
+// complex values of adjacent points) or one point per lane, and the LDS reservation,
+// as store_shape says.
 // Inputs of a complex or spinor launch: in0 (+ in1 for angles) and their kind.
 template <typename TIO>
 struct AnyInputs {
@@ -159,11 +119,10 @@ struct AnyInputs {
 };
 
 template <bool SPINOR, int LMAX, typename TIO, int PPL>
-static hipError_t launch_complex_one(int64_t n, AnyInputs<TIO> in, TIO* out, int64_t ld, hipStream_t s)
+static hipError_t launch_complex_one(int64_t n, AnyInputs<TIO> in, TIO* out, int64_t ld, hipStream_t s, size_t lds)
 {
     const auto kernel = SPINOR ? fwd_spinor_kernel<LMAX, TIO, PPL> : fwd_complex_kernel<LMAX, TIO, PPL>;
-    const unsigned grid = unsigned((n / PPL + kFwdBlock - 1) / kFwdBlock);
-    const size_t lds = PPL * sizeof(TIO) * 2 == 16 ? kCapLds : 0;
+    const unsigned grid = unsigned(((n + PPL - 1) / PPL + kFwdBlock - 1) / kFwdBlock);
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(kFwdBlock), lds, s, in.a, out, uint32_t(n), ld, in.b, in.mode);
     return hipGetLastError();
 }
@@ -173,19 +132,15 @@ static hipError_t launch_complex_one(int64_t n, AnyInputs<TIO> in, TIO* out, int
 template <bool SPINOR, int LMAX, typename TIO>
 static hipError_t launch_complex_l(int64_t n, AnyInputs<TIO> in, TIO* out, int64_t ld, hipStream_t s)
 {
-    constexpr int kVec = sizeof(TIO) == 4 ? 2 : 1;
-    // one point per lane below kFwdVecPoints, as for the real harmonics (FP32 lmax 9,
-    // 4k / 16k / 64k / 100k points: 4.9 / 6.3 / 9.5 / 13.6 us against 6.3 / 7.2 /
-    // 10.2 / 14.1 with two points per lane)
-    const bool vec_ok = n >= kFwdVecPoints && ld % kVec == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0;
+    constexpr int kRows = (SPINOR ? 4 : 1) * nfun(LMAX);
+    constexpr int kVec = sizeof(TIO) == 4 && kRows != 4 ? 2 : 1;  // store_shape never asks 4 rows for more
+    constexpr int64_t kValue = 2 * sizeof(TIO);
+    const StoreShape f = store_shape<kRows, TIO>(n * kRows * kValue, on_lines(out, ld * kValue));
     for (int64_t c0 = 0; c0 < n; c0 += kChunk) {
         const int64_t nc = n - c0 < kChunk ? n - c0 : kChunk;
-        const int64_t nmain = vec_ok ? nc - nc % kVec : 0;
-        hipError_t e = hipSuccess;
-        if (nmain) e = launch_complex_one<SPINOR, LMAX, TIO, kVec>(nmain, in.at(c0), out + 2 * c0, ld, s);
-        if (e == hipSuccess && nmain < nc)
-            e = launch_complex_one<SPINOR, LMAX, TIO, 1>(nc - nmain, in.at(c0 + nmain), out + 2 * (c0 + nmain), ld,
-                                                         s);
+        const hipError_t e = f.wide && nc >= kVec
+                                 ? launch_complex_one<SPINOR, LMAX, TIO, kVec>(nc, in.at(c0), out + 2 * c0, ld, s, f.lds)
+                                 : launch_complex_one<SPINOR, LMAX, TIO, 1>(nc, in.at(c0), out + 2 * c0, ld, s, f.lds);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

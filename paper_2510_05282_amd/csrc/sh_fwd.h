@@ -36,6 +36,68 @@ __device__ __forceinline__ auto& lane(V& v, int k)
     else return reinterpret_cast<scalar_t<V>*>(&v)[k];
 }
 
+// How a launch that stores rows of values is shaped, from what it writes.
+struct StoreShape {
+    bool wide;   // 16 bytes (or more) of adjacent points per lane and row, else one point
+    size_t lds;  // LDS reserved (not used) per 256-thread workgroup
+};
+
+// LDS reservations out of a CU's 160 KiB: at most 3, 2 or 1 resident workgroups.
+constexpr size_t kCapLds3 = 40 * 1024, kCapLds2 = 54 * 1024, kCapLds1 = 84 * 1024;
+
+// Whether rows that start at p and lie row_bytes apart all start on a 128-byte line.
+inline bool on_lines(const void* p, int64_t row_bytes)
+{
+    return row_bytes % 128 == 0 && reinterpret_cast<uintptr_t>(p) % 128 == 0;
+}
+
+// The shape of a launch that writes ROWS rows and `bytes` in all, for the real, complex
+// and spinor harmonics and the Jacobian.  Small outputs stay in the caches on their way
+// out, and such a launch lasts its workgroups' chain of work, which wide lanes lengthen;
+// large ones are bound by the HBM write path, which rewards wide stores and, from 16
+// rows on, few waves at once: the writes under way to each row then lie in a smaller
+// window, and the partial lines that neighbouring waves write where rows do not start on
+// lines merge in the L2.  Measured in us as points per lane / KiB reserved, 3 inputs and
+// outputs in turn (n odd means rows off the lines):
+//  below 2^27 bytes    FP64 lmax 6, 2^18 points (103 MB) 1/0 18.6, 2/54 18.9; FP32 lmax 3,
+//                      2^20 (67 MB) 1/0 12.7, 4/54 13.5; FP32 lmax 9, 2^17 1/0 9.7, 4/54
+//                      10.8; complex FP64 lmax 9, 50001 1/0 13.7, 2/0 21.6
+//  1 row               FP32 2^25 points 4/0 22.1, 4/54 22.8, 1/0 32.0; FP64 equal
+//  4 rows              2^25 points FP64 1/40 307, 1/0 328, 2/54 321; FP32 1/0 156, 4/54
+//                      184; complex 8000001 FP64 1/40 126, 1/54 155, FP32 1/0 67, 2/54 86
+//  9 rows              2^25 points FP64 2/54 563, 2/0 608, 2/84 582; FP32 4/54 283, 4/84
+//                      324; complex 8000001 FP32 2/54 127, 1/0 141, 2/84 156
+//  16 rows and more    n odd: FP64 lmax 9, 2^22 + 1 points 2/84 661, 2/54 748, 2/0 783, 1/0
+//                      857; FP32 lmax 8, 2^23 + 3 4/84 532, 4/54 594, 1/0 820; complex lmax 9,
+//                      1000001 FP64 1/84 328, 1/54 337, FP32 2/84 166, 1/0 191; Jacobian lmax
+//                      9, 1000001 2/84 651, 2/54 708, 1/0 813; n = 1000002 (16- but not
+//                      128-byte aligned) FP64 lmax 9 2/84 164, 2/0 177
+//  the same on lines,  below 2^29 bytes: FP64 lmax 9, 2^19 2/0 77.2, 2/84 80.4; FP32 lmax
+//                      5, 2^21 4/0 61.3, 4/84 63.6; complex FP64 lmax 6, 250000 1/0 38.0,
+//                      1/54 39.3.  Above: FP64 lmax 3, 2^25 2/84 875, 2/54 910, lmax 4 1386,
+//                      1375, lmax 9 at 2^26 68.4% of 8 TB/s against 67.8%; FP32 equal
+constexpr int64_t kWideBytes = int64_t(1) << 27, kCapBytes = int64_t(1) << 29;
+
+template <int ROWS, typename TIO>
+inline StoreShape store_shape(int64_t bytes, bool lines)
+{
+    if (bytes < kWideBytes) return {false, 0};
+    if (ROWS == 1) return {true, 0};
+    if (ROWS <= 4) return {false, sizeof(TIO) == 8 ? kCapLds3 : 0};
+    if (ROWS <= 9) return {true, kCapLds2};
+    if (lines && bytes < kCapBytes) return {true, 0};
+    return {true, !lines || ROWS == 16 || (ROWS > 64 && sizeof(TIO) == 8) ? kCapLds1 : kCapLds2};
+}
+
+// First point of lane `t` of a launch whose lanes take PPL adjacent points of n >= PPL
+// (t * PPL < n): where PPL does not divide n the last lane takes the last PPL points,
+// some of which the lane before it takes too, and both store the same bits.
+template <int PPL>
+__device__ __forceinline__ uint32_t first_point(uint32_t t, uint32_t n)
+{
+    return t * PPL + PPL <= n ? t * PPL : n - PPL;
+}
+
 // The paper's three input interfaces (Section 2): Cartesian points (normalised
 // here), points already on the unit sphere, and the angles (theta, phi).
 enum class In { kXyz, kUnit, kAngles };
@@ -68,9 +130,7 @@ __device__ __forceinline__ void load_unit(const TIO* __restrict__ a, const TIO* 
 // out is [F][ld]; the input is xyz [n][3] (kXyz, kUnit) or theta = xyz[n],
 // phi = in1[n] (kAngles); n * sizeof(TIO) < 2^31 so per-row byte offsets
 // fit 32 bits (the host splits larger batches).  With PPL > 1 the host
-// guarantees n >= PPL; ld and out need no alignment beyond the element's.  Where PPL
-// does not divide n the last lane takes the last PPL points, some of which the lane
-// before it takes too: both store the same bits.
+// guarantees n >= PPL; ld and out need no alignment beyond the element's (first_point).
 template <int LMAX, typename TIO, int PPL, In MODE = In::kXyz>
 __global__ __launch_bounds__(kFwdBlock) void fwd_kernel(const TIO* __restrict__ xyz, TIO* __restrict__ out,
                                                         uint32_t n, int64_t ld, const TIO* __restrict__ in1)
@@ -79,7 +139,7 @@ __global__ __launch_bounds__(kFwdBlock) void fwd_kernel(const TIO* __restrict__ 
     const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
     const uint32_t t = b * kFwdBlock + threadIdx.x;  // vector index
     if (t * PPL >= n) return;
-    const uint32_t i0 = t * PPL + PPL <= n ? t * PPL : n - PPL;  // first point of this lane
+    const uint32_t i0 = first_point<PPL>(t, n);
     V x, y, z, k;
 #pragma unroll
     for (int q = 0; q < PPL; ++q) {
@@ -131,8 +191,8 @@ __device__ __forceinline__ typename vec_of<TIO, 2 * PPL>::type interleave(V re, 
 // Complex harmonics from the real ones (Section 3, complex_unit): out[row][i] as
 // (re, im) pairs, [F][ld] complex.  Each lane evaluates PPL adjacent points and
 // stores their PPL complex values of a row at once: 16 bytes per lane and row for
-// FP64 with PPL = 1 and FP32 with PPL = 2.  With PPL > 1 the host guarantees
-// n % PPL == 0, ld % PPL == 0 and a 16-byte aligned out.  Inputs as for fwd_kernel:
+// FP64 with PPL = 1 and FP32 with PPL = 2.  With PPL > 1 the host guarantees n >= PPL
+// (first_point); ld and out need only the element's alignment.  Inputs as for fwd_kernel:
 // in0 = xyz [n][3] (kXyz, kUnit) or theta[n] and in1 = phi[n] (kAngles).
 template <int LMAX, typename TIO, int PPL>
 __global__ __launch_bounds__(kFwdBlock) void fwd_complex_kernel(const TIO* __restrict__ in0,
@@ -140,9 +200,10 @@ __global__ __launch_bounds__(kFwdBlock) void fwd_complex_kernel(const TIO* __res
                                                                 const TIO* __restrict__ in1, In mode)
 {
     using V = typename vec_of<TIO, PPL>::type;
-    using W = typename vec_of<TIO, 2 * PPL>::type;
-    const uint32_t i0 = (xcd_tile(blockIdx.x, gridDim.x) * kFwdBlock + threadIdx.x) * PPL;
-    if (i0 >= n) return;
+    using W = typename uvec_of<TIO, 2 * PPL>::type;
+    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x) * kFwdBlock + threadIdx.x;
+    if (t * PPL >= n) return;
+    const uint32_t i0 = first_point<PPL>(t, n);
     V x, y, z, k;
     load_points<TIO, PPL>(in0, in1, mode, i0, x, y, z, k);
     const uint32_t boff = i0 * uint32_t(2 * sizeof(TIO));
@@ -161,9 +222,10 @@ __global__ __launch_bounds__(kFwdBlock) void fwd_spinor_kernel(const TIO* __rest
                                                                const TIO* __restrict__ in1, In mode)
 {
     using V = typename vec_of<TIO, PPL>::type;
-    using W = typename vec_of<TIO, 2 * PPL>::type;
-    const uint32_t i0 = (xcd_tile(blockIdx.x, gridDim.x) * kFwdBlock + threadIdx.x) * PPL;
-    if (i0 >= n) return;
+    using W = typename uvec_of<TIO, 2 * PPL>::type;
+    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x) * kFwdBlock + threadIdx.x;
+    if (t * PPL >= n) return;
+    const uint32_t i0 = first_point<PPL>(t, n);
     V x, y, z, k;
     load_points<TIO, PPL>(in0, in1, mode, i0, x, y, z, k);
     const uint32_t boff = i0 * uint32_t(2 * sizeof(TIO));

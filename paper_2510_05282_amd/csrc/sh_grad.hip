@@ -19,6 +19,7 @@
 
 #include "sh_core.h"
 #include "sh_dual.h"
+#include "sh_fwd.h"
 #include "sh_internal.h"
 
 namespace shk {
@@ -102,10 +103,9 @@ template hipError_t launch_grad<float>(int, int64_t, const float*, const float*,
 // jac[(k F + f) ld + i]) in one pass: the dual-number core gives P and grad_u P,
 // which is projected with (1/r)(I - u u^T).  The launch follows the forward
 // kernel's (4F + 3 doubles per point, all but 3 of them row stores): PPL = 2
-// adjacent points per lane with 16-byte row stores, workgroups in XCD-contiguous
-// order, at most 2 resident workgroups per CU; PPL = 1 for odd ld or a
-// remainder point.
-constexpr size_t kJacCapLds = 54 * 1024;
+// adjacent points per lane with 16-byte row stores at any alignment or one point per
+// lane, and the LDS reservation, as store_shape says for 4F rows; workgroups in
+// XCD-contiguous order.
 
 template <int LMAX, int PPL>
 __global__ __launch_bounds__(kGradBlock) void jac_kernel(const double* __restrict__ xyz, double* __restrict__ out,
@@ -113,8 +113,9 @@ __global__ __launch_bounds__(kGradBlock) void jac_kernel(const double* __restric
 {
     constexpr int F = nfun(LMAX);
     using V = std::conditional_t<PPL == 1, double, double2_t>;
-    const uint32_t i0 = (xcd_tile(blockIdx.x, gridDim.x) * kGradBlock + threadIdx.x) * PPL;
-    if (i0 >= n) return;
+    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x) * kGradBlock + threadIdx.x;
+    if (t * PPL >= n) return;
+    const uint32_t i0 = first_point<PPL>(t, n);
     V x, y, z, k, ri;
 #pragma unroll
     for (int q = 0; q < PPL; ++q) {
@@ -129,7 +130,7 @@ __global__ __launch_bounds__(kGradBlock) void jac_kernel(const double* __restric
     }
     const uint32_t boff = i0 * uint32_t(sizeof(double));
     auto at = [&](double* base, int64_t r) {
-        return reinterpret_cast<V*>(reinterpret_cast<char*>(base + r * ld) + boff);
+        return reinterpret_cast<typename uvec_of<double, PPL>::type*>(reinterpret_cast<char*>(base + r * ld) + boff);
     };
     eval_unit_jac<LMAX, V>(x, y, z, k, [&](int f, V v, V gx, V gy, V gz) {
         const V ug = x * gx + y * gy + z * gz;
@@ -141,31 +142,26 @@ __global__ __launch_bounds__(kGradBlock) void jac_kernel(const double* __restric
 }
 
 template <int LMAX, int PPL>
-static hipError_t launch_jac_one(int64_t n, const double* xyz, double* out, double* jac, int64_t ld, hipStream_t s)
+static hipError_t launch_jac_one(int64_t n, const double* xyz, double* out, double* jac, int64_t ld, hipStream_t s,
+                                 size_t lds)
 {
-    const unsigned grid = unsigned((n / PPL + kGradBlock - 1) / kGradBlock);
-    hipLaunchKernelGGL((jac_kernel<LMAX, PPL>), dim3(grid), dim3(kGradBlock), PPL > 1 ? kJacCapLds : 0, s, xyz, out,
-                       jac, uint32_t(n), ld);
+    const unsigned grid = unsigned(((n + PPL - 1) / PPL + kGradBlock - 1) / kGradBlock);
+    hipLaunchKernelGGL((jac_kernel<LMAX, PPL>), dim3(grid), dim3(kGradBlock), lds, s, xyz, out, jac, uint32_t(n), ld);
     return hipGetLastError();
 }
 
 template <int LMAX>
 static hipError_t launch_jac_l(int64_t n, const double* xyz, double* out, double* jac, int64_t ld, hipStream_t s)
 {
-    // several points per lane from 2^18 points on (a smaller launch leaves CUs idle
-    // and lasts one workgroup's chain of work, which the wider lanes lengthen: lmax
-    // 6, 4k / 16k / 64k / 100k points, 7.4 / 9.2 / 16.4 / 24.4 us against 8.6 /
-    // 10.6 / 16.8 / 24.9 with two points per lane)
-    const bool vec_ok = n >= (int64_t(1) << 18) && ld % 2 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0 &&
-                        reinterpret_cast<uintptr_t>(jac) % 16 == 0;
+    constexpr int kRows = 4 * nfun(LMAX);
+    constexpr int kVec = kRows == 4 ? 1 : 2;  // store_shape never asks 4 rows for more
+    const StoreShape f = store_shape<kRows, double>(n * kRows * int64_t(sizeof(double)),
+                                                    on_lines(out, ld * 8) && on_lines(jac, ld * 8));
     for (int64_t c0 = 0; c0 < n; c0 += kGradChunk) {
         const int64_t nc = n - c0 < kGradChunk ? n - c0 : kGradChunk;
-        const int64_t nmain = vec_ok ? nc - nc % 2 : 0;
-        hipError_t e = hipSuccess;
-        if (nmain) e = launch_jac_one<LMAX, 2>(nmain, xyz + 3 * c0, out + c0, jac + c0, ld, s);
-        if (e == hipSuccess && nmain < nc)
-            e = launch_jac_one<LMAX, 1>(nc - nmain, xyz + 3 * (c0 + nmain), out + c0 + nmain, jac + c0 + nmain, ld,
-                                        s);
+        const hipError_t e = f.wide && nc >= kVec
+                                 ? launch_jac_one<LMAX, kVec>(nc, xyz + 3 * c0, out + c0, jac + c0, ld, s, f.lds)
+                                 : launch_jac_one<LMAX, 1>(nc, xyz + 3 * c0, out + c0, jac + c0, ld, s, f.lds);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -21,8 +21,8 @@
 //                 2^(k-1) per XCD, taken in turn by its workgroups (smaller write
 //                 windows per range, more ranges).
 //            `cap` reserves LDS to allow at most 2 workgroups per CU (cap 1, as the
-//            forward kernel does at lmax 2) or 1 (cap 2, as it does for large outputs
-//            from lmax 3 on); `mode` picks the store instruction: 0 global
+//            forward kernel does at FP64 lmax 4 to 7) or 1 (cap 2, as it does at lmax 8, 9
+//            and off the lines); `mode` picks the store instruction: 0 global
 //            store, 1.. buffer stores with cache-policy bits (see kAux).
 //  shp_fwd_split  the lmax 9 FP64 forward kernel with its rows split the same
 //            way: a workgroup evaluates only the harmonics of its row range.

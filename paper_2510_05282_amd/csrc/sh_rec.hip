@@ -55,13 +55,15 @@ __global__ __launch_bounds__(kRecBlock) void rec_kernel(const TIO* __restrict__ 
                                                         uint32_t n, int64_t ld, int lmax)
 {
     using V = typename vec_of<TIO, PPL>::type;
-    const uint32_t i0 = (xcd_tile(blockIdx.x, gridDim.x) * kRecBlock + threadIdx.x) * PPL;
-    if (i0 >= n) return;
+    using U = typename uvec_of<TIO, PPL>::type;
+    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x) * kRecBlock + threadIdx.x;
+    if (t * PPL >= n) return;
+    const uint32_t i0 = first_point<PPL>(t, n);
     V x, y, z, k;
     load_points<TIO, PPL>(xyz, nullptr, In::kXyz, i0, x, y, z, k);
     const uint32_t boff = i0 * uint32_t(sizeof(TIO));
     eval_unit_rec<V>(x, y, z, k, lmax, [&](int l, int m, V v) {
-        *reinterpret_cast<V*>(reinterpret_cast<char*>(out + int64_t(row(l, m)) * ld) + boff) = v;
+        *reinterpret_cast<U*>(reinterpret_cast<char*>(out + int64_t(row(l, m)) * ld) + boff) = v;
     });
 }
 
@@ -110,8 +112,10 @@ __global__ __launch_bounds__(kRecBlock) void grad_rec_kernel(const TIO* __restri
                                                              int lmax)
 {
     using V = typename vec_of<TIO, PPL>::type;
-    const uint32_t i0 = (xcd_tile(blockIdx.x, gridDim.x) * kRecBlock + threadIdx.x) * PPL;
-    if (i0 >= n) return;
+    using U = typename uvec_of<TIO, PPL>::type;
+    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x) * kRecBlock + threadIdx.x;
+    if (t * PPL >= n) return;
+    const uint32_t i0 = first_point<PPL>(t, n);
     double xb[PPL], yb[PPL], zb[PPL], rinv[PPL];
     V x, y, z;
 #pragma unroll
@@ -127,8 +131,8 @@ __global__ __launch_bounds__(kRecBlock) void grad_rec_kernel(const TIO* __restri
     V vx, vy, vz;
     grad_unit_rec<V>(x, y, z, lmax,
                      [&](int r) {
-                         return __builtin_nontemporal_load(reinterpret_cast<const V*>(
-                             reinterpret_cast<const char*>(G + int64_t(r) * ldg) + boff));
+                         return V(__builtin_nontemporal_load(reinterpret_cast<const U*>(
+                             reinterpret_cast<const char*>(G + int64_t(r) * ldg) + boff)));
                      },
                      vx, vy, vz);
     TIO* o = gxyz + 3 * size_t(i0);
@@ -186,9 +190,10 @@ __global__ __launch_bounds__(kRecBlock) void rec_cplx_kernel(const TIO* __restri
                                                              In mode, int lmax)
 {
     using V = typename vec_of<TIO, PPL>::type;
-    using W = typename vec_of<TIO, 2 * PPL>::type;
-    const uint32_t i0 = (xcd_tile(blockIdx.x, gridDim.x) * kRecBlock + threadIdx.x) * PPL;
-    if (i0 >= n) return;
+    using W = typename uvec_of<TIO, 2 * PPL>::type;
+    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x) * kRecBlock + threadIdx.x;
+    if (t * PPL >= n) return;
+    const uint32_t i0 = first_point<PPL>(t, n);
     V x, y, z, k;
     load_points<TIO, PPL>(in0, in1, mode, i0, x, y, z, k);
     const uint32_t boff = i0 * uint32_t(2 * sizeof(TIO));

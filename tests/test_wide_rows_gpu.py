@@ -66,3 +66,28 @@ def test_real_rows_above_the_cap_size(dev):
         y = sh.sh_eval(9, x)
         for i, p in _pieces(lambda v: sh.sh_eval(9, v), x, 150001):
             assert torch.equal(y[:, i:i + p.shape[1]], p)
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("kind,lmax", [("complex", 0), ("complex", 1), ("complex", 2), ("complex", 7), ("spinor", 0),
+                                       ("spinor", 1), ("spinor", 4), ("jac", 0), ("jac", 1), ("jac", 5)])
+@pytest.mark.parametrize("more", [-1, 0, 1])
+def test_other_rows(dev, dtype, kind, lmax, more):
+    if kind == "jac" and dtype == torch.float32:
+        pytest.skip("the Jacobian is FP64 only")
+    size, F = torch.finfo(dtype).bits // 8, (lmax + 1) ** 2
+    per_point = F * size * {"complex": 2, "spinor": 8, "jac": 4}[kind]
+    n = -(-(1 << 27) // per_point) // 2 * 2 + 2 + more  # about 2^27 bytes of output
+    print("case: wide rows,", kind, "lmax", lmax, "n", n, dtype, flush=True)
+    x = _points(n, dtype, dev)
+    if kind == "jac":
+        def fn(v):
+            return torch.cat([t.reshape(-1, v.shape[0]) for t in sh.sh_eval_jac(lmax, v)])
+    else:
+        name = f"sh_eval_{kind}" + ("" if dtype == torch.float64 else "_f32")
+
+        def fn(v):
+            return torch.view_as_real(getattr(sh, name)(lmax, v).reshape(-1, v.shape[0])).movedim(1, -1)
+    y = fn(x)
+    for i, p in _pieces(fn, x, n // 3 + 1):
+        assert torch.equal(y[..., i:i + p.shape[-1]], p)
