@@ -10,45 +10,72 @@
 
 namespace shk {
 
+// The recurrence's coefficients in the order the loops take them, in the arithmetic
+// type S (rounded once from double): for every m the pairs (a, b) of l = m, m + 1, ...
+// with Yb_l = a (z Yb_{l-1} - b Yb_{l-2}).  l = m + 1 is kRecE with b = 0; at l = m,
+// Yb_{m-1} = 0 and Yb_{m-2} = -1 make it d_m = d_m (z 0 - 1 (-1)).  Rows are padded so
+// that a block of up to 8 pairs from any l <= kRecLmax stays inside: a wave reads a
+// block's pairs in one or two scalar loads.
+constexpr int kRecUnroll = 4;
+constexpr int kRecRow = (shc::kRecLmax + 1 + 8 + 7) / 8 * 8;
+template <typename S>
+struct alignas(64) RecTable {
+    S ab[shc::kRecLmax + 1][kRecRow][2];
+    constexpr RecTable() : ab{}
+    {
+        for (int m = 0; m <= shc::kRecLmax; ++m)
+            for (int l = m; l <= shc::kRecLmax; ++l) {
+                ab[m][l - m][0] = S(l == m ? shc::kRecD[m] : l == m + 1 ? shc::kRecE[m] : shc::kRecA[l][m]);
+                ab[m][l - m][1] = S(l == m ? 1.0 : l == m + 1 ? 0.0 : shc::kRecB[l][m]);
+            }
+    }
+};
+template <typename S> constexpr RecTable<S> kRecTable{};
+
 // All (lmax+1)^2 values at the unit vector (x, y, z); store(l, m, value), and for
 // m > 0 the value of +m comes just before that of -m.  keep
 // masks the m = 0 rows of l > 0 at the origin, as in eval_unit.  T is double, float
 // or a clang vector of them (that many points at once).  The loops run over the
-// runtime lmax; every coefficient is a table entry indexed by (l, m) alone, so
-// within a wave it is one scalar load.
+// runtime lmax, kRecUnroll degrees at a time, and over m = part, part + parts, ... only:
+// the values do not depend on how many parts a point is dealt to.
 template <typename T, typename Store>
-__host__ __device__ __forceinline__ void eval_unit_rec(T x, T y, T z, T keep, int lmax, Store&& store)
+__host__ __device__ __forceinline__ void eval_unit_rec(T x, T y, T z, T keep, int lmax, Store&& store, int part = 0,
+                                                       int parts = 1)
 {
-    using S = scalar_t<T>;     // coefficients are rounded once to the arithmetic type
+    using S = scalar_t<T>;
     T c = T(S(1)), s = T(S(0));  // C_m + i S_m = (x + i y)^m
-    for (int m = 0; m <= lmax; ++m) {
-        if (m > 0) {
-            const T cn = x * c - y * s;
-            s = x * s + y * c;
-            c = cn;
-        }
-        const S d = S(shc::kRecD[m]);
-        T y2 = T(S(0)), y1 = T(d);  // Yb_{l-2}^m, Yb_{l-1}^m
-        for (int l = m; l <= lmax; ++l) {
-            T yl;
-            if (l == m) {
-                yl = T(d);
-            } else if (l == m + 1) {
-                yl = S(shc::kRecE[m]) * z * d;
-                y2 = y1;
-                y1 = yl;
-            } else {
-                yl = S(shc::kRecA[l][m]) * (z * y1 - S(shc::kRecB[l][m]) * y2);
-                y2 = y1;
-                y1 = yl;
-            }
+    auto step = [&] {
+        const T cn = x * c - y * s;
+        s = x * s + y * c;
+        c = cn;
+    };
+    for (int m = 0; m < part; ++m) step();
+    for (int m = part; m <= lmax; m += parts) {
+        const auto& row_m = kRecTable<S>.ab[m];
+        auto put = [&](int l, T yl) {
             if (m == 0) {
                 store(l, 0, l > 0 ? yl * keep : yl);
             } else {
                 store(l, m, yl * c);
                 store(l, -m, yl * s);
             }
+        };
+        T y2 = T(S(0)), y1 = T(row_m[0][0]);  // Yb_{l-2}^m, Yb_{l-1}^m
+        put(m, y1);
+        for (int l0 = m + 1; l0 <= lmax; l0 += kRecUnroll) {
+            S a[kRecUnroll], b[kRecUnroll];
+#pragma unroll
+            for (int i = 0; i < kRecUnroll; ++i) a[i] = row_m[l0 - m + i][0], b[i] = row_m[l0 - m + i][1];
+#pragma unroll
+            for (int i = 0; i < kRecUnroll; ++i) {
+                if (l0 + i > lmax) break;
+                const T yl = a[i] * (z * y1 - b[i] * y2);
+                y2 = y1;
+                y1 = yl;
+                put(l0 + i, yl);
+            }
         }
+        for (int k = 0; k < parts; ++k) step();
     }
 }
 
@@ -60,48 +87,63 @@ __host__ __device__ __forceinline__ void eval_unit_rec(T x, T y, T z, T keep, in
 //     d(Pb S_m) = (m Pb S_{m-1},  m Pb C_{m-1}, Pb' S_m),
 // so per m only four sums over l are needed: a = sum G Pb and b = sum G Pb' for the
 // cosine (+m) and sine (-m) rows.  Pb' follows from differentiating the recurrence:
-// Pb_l' = A_l (Pb_{l-1} + z Pb_{l-1}' - B_l Pb_{l-2}').  g(row) returns G[row]; T is
-// double, float or a clang vector of them.
-template <typename T, typename GAt>
-__host__ __device__ __forceinline__ void grad_unit_rec(T x, T y, T z, int lmax, GAt&& g, T& vx, T& vy, T& vz)
+// Pb_l' = A_l (Pb_{l-1} + z Pb_{l-1}' - B_l Pb_{l-2}').  The m are dealt to kRecParts
+// parts, m = part, part + kRecParts, ..., which one lane each can take at the same time
+// (their rows are then read by as many waves); grad_unit_rec_sum adds them up, always in
+// the same order.  g(row) returns G[row], asked for a block of UNROLL degrees before the
+// first is used, so that many reads are under way at once; T is double, float or a
+// clang vector of them.
+constexpr int kRecParts = 4;
+template <typename T, int UNROLL, typename GAt>
+__host__ __device__ __forceinline__ void grad_unit_rec_part(T x, T y, T z, int lmax, int part, GAt&& g, T& vx, T& vy,
+                                                            T& vz)
 {
+    static_assert(UNROLL <= 8, "the table's rows are padded for 8");
     using S = scalar_t<T>;
     const T zero = T(S(0));
     vx = zero;
     vy = zero;
     vz = zero;
-    T c = T(S(1)), s = zero;  // C_m, S_m
-    for (int m = 0; m <= lmax; ++m) {
-        const T cp = c, sp = s;  // C_{m-1}, S_{m-1}
-        if (m > 0) {
-            c = x * cp - y * sp;
-            s = x * sp + y * cp;
-        }
-        const S d = S(shc::kRecD[m]);
-        T y1 = T(d), dy1 = zero, y2 = zero, dy2 = zero;  // Pb_{l-1}, Pb'_{l-1}, Pb_{l-2}, Pb'_{l-2}
+    T c = T(S(1)), s = zero, cp = zero, sp = zero;  // C_m, S_m, C_{m-1}, S_{m-1}
+    auto step = [&] {
+        cp = c;
+        sp = s;
+        c = x * cp - y * sp;
+        s = x * sp + y * cp;
+    };
+    for (int m = 0; m < part; ++m) step();
+    for (int m = part; m <= lmax; m += kRecParts) {
+        const auto& row_m = kRecTable<S>.ab[m];
+        T y1 = zero, dy1 = zero, y2 = T(S(-1)), dy2 = zero;  // Pb_{l-1}, Pb'_{l-1}, Pb_{l-2}, Pb'_{l-2}
         T ac = zero, bc = zero, as = zero, bs = zero;
-        for (int l = m; l <= lmax; ++l) {
-            T yl, dl;
-            if (l == m) {
-                yl = T(d);
-                dl = zero;
-            } else {
-                const S a = l == m + 1 ? S(shc::kRecE[m]) : S(shc::kRecA[l][m]);
-                const S b = l == m + 1 ? S(0) : S(shc::kRecB[l][m]);
-                yl = a * (z * y1 - b * y2);
-                dl = a * (y1 + z * dy1 - b * dy2);
+        for (int l0 = m; l0 <= lmax; l0 += UNROLL) {
+            S a[UNROLL], b[UNROLL];
+            T gc[UNROLL], gs[UNROLL];
+#pragma unroll
+            for (int i = 0; i < UNROLL; ++i) {
+                // beyond lmax the last row again, as 0: a branch around each read would
+                // have it waited for before the next is issued
+                const int l = l0 + i <= lmax ? l0 + i : lmax;
+                a[i] = row_m[l0 - m + i][0], b[i] = row_m[l0 - m + i][1];
+                gc[i] = g(row(l, m));
+                gs[i] = g(row(l, -m));
+            }
+#ifdef __HIP_DEVICE_COMPILE__
+            __builtin_amdgcn_sched_barrier(0);  // the reads stay ahead of the arithmetic
+#endif
+#pragma unroll
+            for (int i = 0; i < UNROLL; ++i) {
+                const T yl = a[i] * (z * y1 - b[i] * y2);
+                const T dl = a[i] * (y1 + z * dy1 - b[i] * dy2);
                 y2 = y1;
                 dy2 = dy1;
                 y1 = yl;
                 dy1 = dl;
-            }
-            const T gc = g(row(l, m));
-            ac += gc * yl;
-            bc += gc * dl;
-            if (m > 0) {
-                const T gs = g(row(l, -m));
-                as += gs * yl;
-                bs += gs * dl;
+                const T c_l = l0 + i <= lmax ? gc[i] : zero, s_l = l0 + i <= lmax ? gs[i] : zero;
+                ac += c_l * yl;
+                bc += c_l * dl;
+                as += s_l * yl;
+                bs += s_l * dl;
             }
         }
         if (m == 0) {
@@ -112,6 +154,30 @@ __host__ __device__ __forceinline__ void grad_unit_rec(T x, T y, T z, int lmax, 
             vy += fm * (as * cp - ac * sp);
             vz += bc * c + bs * s;
         }
+        for (int k = 0; k < kRecParts; ++k) step();
+    }
+}
+
+// The sum of the parts, from v(part).
+template <typename GetPart>
+__host__ __device__ __forceinline__ auto grad_unit_rec_sum(GetPart&& v)
+{
+    static_assert(kRecParts == 4, "two pairs");
+    return (v(0) + v(1)) + (v(2) + v(3));
+}
+
+// All of v by one lane: the same sum, a pair at a time.
+template <typename T, int UNROLL = 2, typename GAt>
+__host__ __device__ __forceinline__ void grad_unit_rec(T x, T y, T z, int lmax, GAt&& g, T& vx, T& vy, T& vz)
+{
+#pragma unroll 1
+    for (int p = 0; p < kRecParts; p += 2) {
+        T ax, ay, az, bx, by, bz;
+        grad_unit_rec_part<T, UNROLL>(x, y, z, lmax, p, g, ax, ay, az);
+        grad_unit_rec_part<T, UNROLL>(x, y, z, lmax, p + 1, g, bx, by, bz);
+        vx = p == 0 ? ax + bx : vx + (ax + bx);
+        vy = p == 0 ? ay + by : vy + (ay + by);
+        vz = p == 0 ? az + bz : vz + (az + bz);
     }
 }
 

@@ -14,10 +14,7 @@
 // whose coefficients are generated once (gen_rec_constants.py, 50-digit mpmath),
 // so the kernel does no square roots or divisions.  Same normalisation, origin
 // guard and [F][ld] layout as the explicit kernels, FP64 or FP32 (normalisation
-// in FP64 either way), lmax up to SH_LMAX_REC.  The launch follows the explicit
-// kernel's: 16-byte row stores per lane (two FP64 or four FP32 adjacent points),
-// XCD-contiguous workgroups, at most 2 resident workgroups per CU; one point per
-// lane for an unaligned row stride or the remainder points.
+// in FP64 either way), lmax up to SH_LMAX_REC.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -35,59 +32,67 @@ static_assert(shc::kRecLmax == SH_LMAX_REC, "recurrence tables and the public li
 
 constexpr int kRecBlock = 256;
 constexpr int64_t kRecChunk = int64_t(1) << 28;
-// Calls of at least this many points take several points per lane; smaller
-// launches leave CUs idle and last one workgroup's chain of work, which the wider
-// lanes lengthen, so they run one point per lane.  Kernel trace, 4k / 16k / 64k /
-// 100k points, one point per lane against the wide lanes: real harmonics at lmax
-// 16 FP64 25.1 / 27.3 / 33.1 / 48.5 us against 30.3 / 32.3 / 37.2 / 44.5, FP32
-// 24.6 / 29.2 / 35.3 / 35.7 against 36.0 / 40.2 / 45.4 / 45.6; the backward pass at
-// lmax 14 FP64 38.2 / 74.1 / 76.9 / 83.9 against 44.2 / 83.2 / 85.9 / 88.0; equal
-// at 2^18 points.  The FP64 forward switches between 64k and 100k points.
-// (real harmonics; the complex and spinor forms and the backward pass switch at 2^18)
-template <typename TIO> constexpr int64_t kRecVecPoints = sizeof(TIO) == 8 ? int64_t(3) << 15 : int64_t(1) << 18;
-constexpr int64_t kRecVecPointsCplxGrad = int64_t(1) << 18;
-constexpr size_t kRecCapLds = 54 * 1024;
 
-// TIO = double: 2 points per lane (PPL = 2); float: 4 (PPL = 4); both store 16
-// bytes per lane and row.  Points are normalised in FP64 either way.
-template <typename TIO, int PPL>
+// TIO = double: up to 2 points per lane (PPL = 2); float: 4 (PPL = 4); both then store
+// 16 bytes per lane and row.  Points are normalised in FP64 either way.  SPLIT: the
+// workgroup takes 64 lanes' worth of points and deals their m to its four waves.
+template <typename TIO, int PPL, bool SPLIT>
 __global__ __launch_bounds__(kRecBlock) void rec_kernel(const TIO* __restrict__ xyz, TIO* __restrict__ out,
                                                         uint32_t n, int64_t ld, int lmax)
 {
     using V = typename vec_of<TIO, PPL>::type;
     using U = typename uvec_of<TIO, PPL>::type;
-    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x) * kRecBlock + threadIdx.x;
+    constexpr int kLanes = SPLIT ? 64 : kRecBlock;
+    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x) * kLanes + threadIdx.x % kLanes;
     if (t * PPL >= n) return;
     const uint32_t i0 = first_point<PPL>(t, n);
     V x, y, z, k;
     load_points<TIO, PPL>(xyz, nullptr, In::kXyz, i0, x, y, z, k);
     const uint32_t boff = i0 * uint32_t(sizeof(TIO));
-    eval_unit_rec<V>(x, y, z, k, lmax, [&](int l, int m, V v) {
+    auto store = [&](int l, int m, V v) {
         *reinterpret_cast<U*>(reinterpret_cast<char*>(out + int64_t(row(l, m)) * ld) + boff) = v;
-    });
+    };
+    if constexpr (SPLIT)
+        eval_unit_rec<V>(x, y, z, k, lmax, store, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kRecBlock / 64);
+    else
+        eval_unit_rec<V>(x, y, z, k, lmax, store);
 }
 
-template <typename TIO, int PPL>
-static hipError_t launch_rec_one(int lmax, int64_t n, const TIO* xyz, TIO* out, int64_t ld, hipStream_t s)
+template <typename TIO, int PPL, bool SPLIT>
+static hipError_t launch_rec_one(int lmax, int64_t n, const TIO* xyz, TIO* out, int64_t ld, hipStream_t s, size_t lds)
 {
-    const unsigned grid = unsigned((n / PPL + kRecBlock - 1) / kRecBlock);
-    hipLaunchKernelGGL((rec_kernel<TIO, PPL>), dim3(grid), dim3(kRecBlock), PPL > 1 ? kRecCapLds : 0, s, xyz, out,
-                       uint32_t(n), ld, lmax);
+    constexpr int kLanes = SPLIT ? 64 : kRecBlock;
+    const unsigned grid = unsigned(((n + PPL - 1) / PPL + kLanes - 1) / kLanes);
+    hipLaunchKernelGGL((rec_kernel<TIO, PPL, SPLIT>), dim3(grid), dim3(kRecBlock), lds, s, xyz, out, uint32_t(n), ld,
+                       lmax);
     return hipGetLastError();
 }
+
+// How the forward launches are shaped (us, points per lane / KiB of LDS reserved; a
+// launch that writes less than kWideBytes takes one point per lane, as store_shape):
+//   below 2^16 points  the m dealt to four waves: such a launch is one chain of work long:
+//                      10001 points, lmax 16 FP64 26.9 -> 8.6, FP32 25.3 -> 7.4 (12 MB)
+//   wide, 2^19 points  off the lines (see store_shape): 1000001 points, lmax 16 FP64 2/84
+//                      485, 2/54 500, 1/0 598; FP32, 2000001 4/84 473, 4/54 515
+//   wide otherwise     200001 points, lmax 16 FP64 2/54 88, 2/84 114 (one workgroup per CU
+//                      leaves a short last round); FP32 4/54 47; 4000000 FP64 2/54 1730,
+//                      2/84 1761
+constexpr int64_t kRecSplitPoints = int64_t(1) << 16, kRecCapPoints = int64_t(1) << 19;
+inline size_t rec_lds(int64_t n, bool lines) { return !lines && n >= kRecCapPoints ? kCapLds1 : kCapLds2; }
 
 template <typename TIO>
 hipError_t launch_rec(int lmax, int64_t n, const TIO* xyz, TIO* out, int64_t ld, hipStream_t s)
 {
     constexpr int kVec = 16 / sizeof(TIO);
-    const bool vec_ok = n >= kRecVecPoints<TIO> && ld % kVec == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0;
+    const int64_t bytes = n * nfun(lmax) * int64_t(sizeof(TIO));
+    const bool wide = bytes >= kWideBytes;
+    const size_t lds = wide ? rec_lds(n, on_lines(out, ld * sizeof(TIO))) : 0;
     for (int64_t c0 = 0; c0 < n; c0 += kRecChunk) {
         const int64_t nc = n - c0 < kRecChunk ? n - c0 : kRecChunk;
-        const int64_t nmain = vec_ok ? nc - nc % kVec : 0;
-        hipError_t e = hipSuccess;
-        if (nmain) e = launch_rec_one<TIO, kVec>(lmax, nmain, xyz + 3 * c0, out + c0, ld, s);
-        if (e == hipSuccess && nmain < nc)
-            e = launch_rec_one<TIO, 1>(lmax, nc - nmain, xyz + 3 * (c0 + nmain), out + c0 + nmain, ld, s);
+        const TIO* x = xyz + 3 * c0;
+        const hipError_t e = wide && nc >= kVec   ? launch_rec_one<TIO, kVec, false>(lmax, nc, x, out + c0, ld, s, lds)
+                             : n < kRecSplitPoints ? launch_rec_one<TIO, 1, true>(lmax, nc, x, out + c0, ld, s, 0)
+                                                   : launch_rec_one<TIO, 1, false>(lmax, nc, x, out + c0, ld, s, 0);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -99,23 +104,38 @@ template hipError_t launch_rec<float>(int, int64_t, const float*, float*, int64_
 // Backward pass by recurrence: the vector-Jacobian product of sh_eval_rec,
 //     g = (1/r) (v - u (u . v)),   v = sum_rows G[row] grad_u P_row(u),
 // as the explicit backward kernel, with v from grad_unit_rec (the recurrence
-// differentiated in z, the xy factors by their closed-form partials).  PPL
-// adjacent points per lane (G read as one PPL-wide vector per row: 16 bytes in
-// FP64, 8 in FP32, where four points per lane need 140 VGPRs and ran slower, and one
-// point per lane reached 53% of 8 TB/s at lmax 16 against 68% with two),
-// workgroups in XCD-contiguous order, no cap on resident workgroups (capping to
-// 2 or 4 per CU loses 25-50% here: the kernel needs many loads in flight); the
-// normalisation and 1/r in FP64.
-template <typename TIO, int PPL>
-__global__ __launch_bounds__(kRecBlock) void grad_rec_kernel(const TIO* __restrict__ xyz, const TIO* __restrict__ G,
-                                                             TIO* __restrict__ gxyz, uint32_t n, int64_t ldg,
-                                                             int lmax)
+// differentiated in z, the xy factors by their closed-form partials).  PPL adjacent
+// points per lane, whose values of a row of G are one read at any alignment; UNROLL
+// degrees' reads issued together; workgroups in XCD-contiguous order; the normalisation
+// and 1/r in FP64.  SPLIT: a workgroup takes 64 lanes' worth of points, its four waves a
+// quarter of the m each, and one wave adds the four sums up; otherwise a lane goes
+// through the quarters itself.  The sums are the same either way.
+// Bound by the reads of G, and by their latency wherever few waves have few reads under
+// way: with every read waited for before the next and no split, 200001 points at lmax 16
+// took 124 us in FP64 (3.8 TB/s) and 110 in FP32 (2.1), 10001 points 84 and 75; now 81
+// (5.8 TB/s), 47 (5.0), 11 and 10.
+// Which one, in us as SPLIT or not, points per lane, reads unrolled by (lmax 16):
+//   below 2^16 points  10001: FP64 split 1 x 8 11.0, 1 x 2 16.6, 2 x 2 18.9; FP32 10.1, 15.0, 17.7
+//   then, split 2 x 2  200001: FP64 split 2 x 2 81, whole 2 x 2 79-85, whole 1 x 1 107; FP32
+//                      split 47, whole 4 x 2 69; 800001: FP32 split 178, whole 4 x 2 204
+//   from 2^18 (FP64)   520001: whole 2 x 2 208 (held to 128 registers, four waves a SIMD;
+//                      238 at 130), split 272; 2000001: whole 831, split 858
+//   from 2^20 (FP32)   2000001: whole 4 x 2 393, whole 2 x 2 433, split 447
+constexpr int64_t kGradRecNarrow = int64_t(1) << 16;
+template <typename TIO> constexpr int64_t kGradRecSplit = int64_t(1) << (sizeof(TIO) == 8 ? 18 : 20);
+
+template <typename TIO, int PPL, bool SPLIT, int UNROLL>
+__global__ __launch_bounds__(kRecBlock, !SPLIT && sizeof(TIO) == 8 ? 4 : 1) void grad_rec_kernel(
+    const TIO* __restrict__ xyz, const TIO* __restrict__ G, TIO* __restrict__ gxyz, uint32_t n, int64_t ldg, int lmax)
 {
     using V = typename vec_of<TIO, PPL>::type;
     using U = typename uvec_of<TIO, PPL>::type;
-    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x) * kRecBlock + threadIdx.x;
-    if (t * PPL >= n) return;
-    const uint32_t i0 = first_point<PPL>(t, n);
+    static_assert(kRecBlock == 64 * kRecParts, "one wave per part");
+    constexpr int kLanes = SPLIT ? 64 : kRecBlock;  // lanes' worth of points per workgroup
+    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x) * kLanes + threadIdx.x % kLanes;
+    const bool live = t * PPL < n;
+    if (!SPLIT && !live) return;
+    const uint32_t i0 = live ? first_point<PPL>(t, n) : 0;
     double xb[PPL], yb[PPL], zb[PPL], rinv[PPL];
     V x, y, z;
 #pragma unroll
@@ -128,18 +148,29 @@ __global__ __launch_bounds__(kRecBlock) void grad_rec_kernel(const TIO* __restri
         lane<V, PPL>(z, q) = TIO(zb[q]);
     }
     const uint32_t boff = i0 * uint32_t(sizeof(TIO));
-    V vx, vy, vz;
-    grad_unit_rec<V>(x, y, z, lmax,
-                     [&](int r) {
-                         return V(__builtin_nontemporal_load(reinterpret_cast<const U*>(
-                             reinterpret_cast<const char*>(G + int64_t(r) * ldg) + boff)));
-                     },
-                     vx, vy, vz);
+    auto g_at = [&](int r) {
+        return V(__builtin_nontemporal_load(
+            reinterpret_cast<const U*>(reinterpret_cast<const char*>(G + int64_t(r) * ldg) + boff)));
+    };
+    V v[3];
+    if constexpr (SPLIT) {
+        __shared__ V parts[kRecParts][3][64];
+        const int wl = threadIdx.x & 63, part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        grad_unit_rec_part<V, UNROLL>(x, y, z, lmax, part, g_at, v[0], v[1], v[2]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) parts[part][k][wl] = v[k];
+        __syncthreads();
+        if (part != 0 || !live) return;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) v[k] = grad_unit_rec_sum([&](int p) { return p == 0 ? v[k] : parts[p][k][wl]; });
+    } else {
+        grad_unit_rec<V, UNROLL>(x, y, z, lmax, g_at, v[0], v[1], v[2]);
+    }
     TIO* o = gxyz + 3 * size_t(i0);
 #pragma unroll
     for (int q = 0; q < PPL; ++q) {
-        const double gx = double(lane<V, PPL>(vx, q)), gy = double(lane<V, PPL>(vy, q)),
-                     gz = double(lane<V, PPL>(vz, q));
+        const double gx = double(lane<V, PPL>(v[0], q)), gy = double(lane<V, PPL>(v[1], q)),
+                     gz = double(lane<V, PPL>(v[2], q));
         const double uv = xb[q] * gx + yb[q] * gy + zb[q] * gz;
         o[3 * q + 0] = TIO(rinv[q] * (gx - xb[q] * uv));
         o[3 * q + 1] = TIO(rinv[q] * (gy - yb[q] * uv));
@@ -147,32 +178,29 @@ __global__ __launch_bounds__(kRecBlock) void grad_rec_kernel(const TIO* __restri
     }
 }
 
-// n must be a multiple of PPL (the caller sends the remainder to PPL = 1).
-template <typename TIO, int PPL>
+template <typename TIO, int PPL, bool SPLIT, int UNROLL>
 static hipError_t launch_grad_rec_one(int lmax, int64_t n, const TIO* xyz, const TIO* G, int64_t ldg, TIO* gxyz,
                                       hipStream_t s)
 {
-    const unsigned grid = unsigned((n / PPL + kRecBlock - 1) / kRecBlock);
-    hipLaunchKernelGGL((grad_rec_kernel<TIO, PPL>), dim3(grid), dim3(kRecBlock), 0, s, xyz, G, gxyz, uint32_t(n),
-                       ldg, lmax);
+    constexpr int kLanes = SPLIT ? 64 : kRecBlock;
+    const unsigned grid = unsigned(((n + PPL - 1) / PPL + kLanes - 1) / kLanes);
+    hipLaunchKernelGGL((grad_rec_kernel<TIO, PPL, SPLIT, UNROLL>), dim3(grid), dim3(kRecBlock), 0, s, xyz, G, gxyz,
+                       uint32_t(n), ldg, lmax);
     return hipGetLastError();
 }
 
 template <typename TIO>
 hipError_t launch_grad_rec(int lmax, int64_t n, const TIO* xyz, const TIO* G, int64_t ldg, TIO* gxyz, hipStream_t s)
 {
-    constexpr int kVec = 2;
-    const bool vec_ok =
-        n >= kRecVecPointsCplxGrad && ldg % kVec == 0 && reinterpret_cast<uintptr_t>(G) % (kVec * sizeof(TIO)) == 0;
-    for (int64_t c0 = 0; c0 < n; c0 += kRecChunk) {  // kRecChunk is a multiple of kVec
+    constexpr int kVec = 16 / sizeof(TIO);
+    for (int64_t c0 = 0; c0 < n; c0 += kRecChunk) {
         const int64_t nc = n - c0 < kRecChunk ? n - c0 : kRecChunk;
-        const int64_t nmain = vec_ok ? nc - nc % kVec : 0;
-        hipError_t e = hipSuccess;
-        if (nmain) e = launch_grad_rec_one<TIO, kVec>(lmax, nmain, xyz + 3 * c0, G + c0, ldg, gxyz + 3 * c0, s);
-        if (e == hipSuccess && nc > nmain) {
-            const int64_t c1 = c0 + nmain;
-            e = launch_grad_rec_one<TIO, 1>(lmax, nc - nmain, xyz + 3 * c1, G + c1, ldg, gxyz + 3 * c1, s);
-        }
+        const TIO *x = xyz + 3 * c0, *g = G + c0;
+        TIO* o = gxyz + 3 * c0;
+        const hipError_t e =
+            n < kGradRecNarrow || nc < kVec ? launch_grad_rec_one<TIO, 1, true, 8>(lmax, nc, x, g, ldg, o, s)
+            : n < kGradRecSplit<TIO>        ? launch_grad_rec_one<TIO, 2, true, 2>(lmax, nc, x, g, ldg, o, s)
+                                            : launch_grad_rec_one<TIO, kVec, false, 2>(lmax, nc, x, g, ldg, o, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -208,10 +236,9 @@ __global__ __launch_bounds__(kRecBlock) void rec_cplx_kernel(const TIO* __restri
 
 template <typename TIO, int PPL, bool SPINOR>
 static hipError_t launch_rec_cplx_one(int lmax, int64_t n, In mode, const TIO* a, const TIO* b, TIO* out,
-                                      int64_t ld, hipStream_t s)
+                                      int64_t ld, hipStream_t s, size_t lds)
 {
-    const unsigned grid = unsigned((n / PPL + kRecBlock - 1) / kRecBlock);
-    const size_t lds = PPL * sizeof(TIO) * 2 == 16 ? kRecCapLds : 0;
+    const unsigned grid = unsigned(((n + PPL - 1) / PPL + kRecBlock - 1) / kRecBlock);
     hipLaunchKernelGGL((rec_cplx_kernel<TIO, PPL, SPINOR>), dim3(grid), dim3(kRecBlock), lds, s, a, out,
                        uint32_t(n), ld, b, mode, lmax);
     return hipGetLastError();
@@ -222,19 +249,18 @@ static hipError_t launch_rec_cplx(int lmax, int64_t n, int input, const TIO* in0
                                   int64_t ld, hipStream_t s)
 {
     constexpr int kVec = sizeof(TIO) == 4 ? 2 : 1;
+    constexpr int64_t kValue = 2 * sizeof(TIO);
     const In mode = In(input);
     const int64_t stride = mode == In::kAngles ? 1 : 3;
-    const bool vec_ok = n >= kRecVecPointsCplxGrad && ld % kVec == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0;
+    const bool wide = n * nfun(lmax) * (SPINOR ? 4 : 1) * kValue >= kWideBytes;
+    const size_t lds = wide ? rec_lds(n, on_lines(out, ld * kValue)) : 0;
     for (int64_t c0 = 0; c0 < n; c0 += kRecChunk) {
         const int64_t nc = n - c0 < kRecChunk ? n - c0 : kRecChunk;
-        const int64_t nmain = vec_ok ? nc - nc % kVec : 0;
-        auto a = [&](int64_t c) { return in0 + stride * c; };
-        auto b = [&](int64_t c) { return mode == In::kAngles ? in1 + c : in1; };
-        hipError_t e = hipSuccess;
-        if (nmain) e = launch_rec_cplx_one<TIO, kVec, SPINOR>(lmax, nmain, mode, a(c0), b(c0), out + 2 * c0, ld, s);
-        if (e == hipSuccess && nmain < nc)
-            e = launch_rec_cplx_one<TIO, 1, SPINOR>(lmax, nc - nmain, mode, a(c0 + nmain), b(c0 + nmain),
-                                                    out + 2 * (c0 + nmain), ld, s);
+        const TIO *a = in0 + stride * c0, *b = mode == In::kAngles ? in1 + c0 : in1;
+        const hipError_t e =
+            wide && nc >= kVec
+                ? launch_rec_cplx_one<TIO, kVec, SPINOR>(lmax, nc, mode, a, b, out + 2 * c0, ld, s, lds)
+                : launch_rec_cplx_one<TIO, 1, SPINOR>(lmax, nc, mode, a, b, out + 2 * c0, ld, s, lds);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -1,0 +1,83 @@
+"""The recurrence's launches by size: the m of a point dealt to four waves or taken by one
+lane, one or several points per lane, reads in blocks of 2 or 8 degrees.  A point's values
+and gradient are the same bits whichever runs, and small calls agree with the oracle (FP64
+1e-12 in the values, 1e-12 (1 + |g|) in the gradient; FP32 1e-6 (l + 1) and 5e-6 (l + 1)
+(1 + |g|), the bounds of the header)."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2510_05282_amd as sh
+
+pytestmark = pytest.mark.gpu
+DTYPES = [torch.float64, torch.float32]
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+def _inputs(n, lmax, dtype, dev):
+    g = torch.Generator(device=dev)
+    g.manual_seed(n + lmax)
+    x = torch.randn((n, 3), generator=g, dtype=torch.float64, device=dev)
+    x = x / x.norm(dim=1, keepdim=True) * (0.5 + 2.0 * torch.rand((n, 1), generator=g, dtype=torch.float64, device=dev))
+    if n > 4:
+        x[n // 2] = 0.0
+    G = torch.randn(((lmax + 1) ** 2, n), generator=g, dtype=dtype, device=dev)
+    return x.to(dtype).contiguous(), G
+
+
+def _fns(dtype):
+    return ((sh.sh_eval_rec, sh.sh_eval_grad_rec) if dtype == torch.float64
+            else (sh.sh_eval_rec_f32, sh.sh_eval_grad_rec_f32))
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 64, 65, 257])
+@pytest.mark.parametrize("lmax", [0, 1, 2, 3, 4, 7, 8, 9, 15, 24])
+def test_small_against_the_oracle(dev, orc, dtype, n, lmax):
+    print("case: recurrence, n", n, "lmax", lmax, dtype, flush=True)
+    x, G = _inputs(n, lmax, dtype, dev)
+    fwd, bwd = _fns(dtype)
+    y, g = fwd(lmax, x).cpu().numpy(), bwd(lmax, x, G).cpu().numpy()
+    xd, Gd = x.double().cpu().numpy(), G.double().cpu().numpy()
+    ref, gref = orc.eval_xyz(lmax, xd), orc.grad_xyz(lmax, xd, Gd)
+    scale = 1.0 + np.abs(gref.astype(np.float64)).max(axis=1, keepdims=True)
+    tol, gtol = (1e-12, 1e-12) if dtype == torch.float64 else (max(5e-6, 1e-6 * (lmax + 1)), 5e-6 * (lmax + 1))
+    assert np.abs(y.astype(np.longdouble) - ref).max() <= tol
+    assert (np.abs(g.astype(np.longdouble) - gref) / scale).max() <= gtol
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("n,lmax", [((1 << 16) - 1, 12), (1 << 16, 12), ((1 << 16) + 1, 17), (100003, 16),
+                                    ((1 << 18) - 1, 11), ((1 << 18) + 1, 11), ((1 << 19) + 3, 10), ((1 << 19) + 64, 10),
+                                    ((1 << 20) + 1, 6), (1 << 20, 3)])
+def test_launches_agree(dev, dtype, n, lmax):
+    print("case: recurrence launches, n", n, "lmax", lmax, dtype, flush=True)
+    x, G = _inputs(n, lmax, dtype, dev)
+    fwd, bwd = _fns(dtype)
+    y, g = fwd(lmax, x), bwd(lmax, x, G)
+    piece = 65535  # below every other launch's size
+    for i in range(0, n, piece):
+        p = x[i:i + piece].contiguous()
+        assert torch.equal(y[:, i:i + piece], fwd(lmax, p))
+        assert torch.equal(g[i:i + piece], bwd(lmax, p, G[:, i:i + piece].contiguous()))
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("n", [116161, 116163, (1 << 19) + 5])
+def test_complex_launches_agree(dev, dtype, n):
+    """Complex harmonics by recurrence around 2^27 bytes of output (lmax 11 in FP32, 8 in FP64)."""
+    lmax = 8 if dtype == torch.float64 else 11
+    print("case: complex recurrence launches, n", n, dtype, flush=True)
+    x, _ = _inputs(n, lmax, dtype, dev)
+    y = sh.sh_eval_complex_rec(lmax, x)
+    for i in range(0, n, 50001):
+        p = sh.sh_eval_complex_rec(lmax, x[i:i + 50001].contiguous())
+        assert torch.equal(torch.view_as_real(y[:, i:i + 50001]), torch.view_as_real(p))
