@@ -144,49 +144,26 @@ __device__ __forceinline__ void proj_point(double px, double py, double pz, cons
                          [&](int f, TIO v) { out[int64_t(f) * stride] = R[l_of_row(f)] * v; });
 }
 
-// Stores the PPL values of vector o (adjacent points) to dst[0 .. PPL-1] with the
-// widest stores the alignment allows: H leading elements one by one up to a
-// 16-byte boundary, 16-byte vectors, then the rest one by one (H is a
-// compile-time case of the run's alignment).
-template <typename TIO, int PPL, int H, typename V>
-__device__ __forceinline__ void store_run_from(TIO* __restrict__ dst, V o)
-{
-    constexpr int UNIT = 16 / int(sizeof(TIO));
-    constexpr int NVEC = H < PPL ? (PPL - H) / UNIT : 0;
-    static_for<0, (H < PPL ? H : PPL)>([&](auto qc) {
-        constexpr int q = decltype(qc)::value;
-        dst[q] = lane<V, PPL>(o, q);
-    });
-    static_for<0, NVEC>([&](auto kc) {
-        constexpr int i0 = H + decltype(kc)::value * UNIT;
-        typename vec_of<TIO, UNIT>::type w;
-        static_for<0, UNIT>([&](auto uc) {
-            constexpr int u = decltype(uc)::value;
-            w[u] = lane<V, PPL>(o, i0 + u);
-        });
-        *reinterpret_cast<typename vec_of<TIO, UNIT>::type*>(dst + i0) = w;
-    });
-    static_for<(H < PPL ? H : PPL) + NVEC * UNIT, PPL>([&](auto qc) {
-        constexpr int q = decltype(qc)::value;
-        dst[q] = lane<V, PPL>(o, q);
-    });
-}
-
-// The first nvalid of the PPL values of o to dst (element-aligned).
+// The first nvalid of the PPL values of o (adjacent points) to dst: 16-byte stores at
+// any element alignment where all of them are wanted, else one by one.
 template <typename TIO, int PPL, typename V>
 __device__ __forceinline__ void store_run(TIO* __restrict__ dst, V o, int nvalid)
 {
-    constexpr int UNIT = 16 / int(sizeof(TIO));
-    if (nvalid < PPL || PPL < UNIT) {
+    constexpr int UNIT = 16 / int(sizeof(TIO)) < PPL ? 16 / int(sizeof(TIO)) : PPL;
+    if (nvalid < PPL) {
 #pragma unroll
         for (int q = 0; q < PPL; ++q)
             if (q < nvalid) dst[q] = lane<V, PPL>(o, q);
         return;
     }
-    const int a = int((reinterpret_cast<uintptr_t>(dst) / sizeof(TIO)) & (UNIT - 1));
-    const int head = (UNIT - a) & (UNIT - 1);
-    static_for<0, UNIT>([&](auto hc) {
-        if (head == decltype(hc)::value) store_run_from<TIO, PPL, decltype(hc)::value>(dst, o);
+    static_for<0, PPL / UNIT>([&](auto kc) {
+        constexpr int i0 = decltype(kc)::value * UNIT;
+        typename uvec_of<TIO, UNIT>::type w;
+        static_for<0, UNIT>([&](auto uc) {
+            constexpr int u = decltype(uc)::value;
+            w[u] = lane<V, PPL>(o, i0 + u);
+        });
+        *reinterpret_cast<typename uvec_of<TIO, UNIT>::type*>(dst + i0) = w;
     });
 }
 
@@ -194,8 +171,7 @@ __device__ __forceinline__ void store_run(TIO* __restrict__ dst, V o, int nvalid
 // (the polynomials on PPL-wide vectors, which keeps more independent work in each
 // lane): point q's coordinates are (px[q], py[q], pz[q]) and row f of point q goes
 // to out[f * stride + q], for the first nvalid points only (the others are computed
-// and dropped, so a tail lane runs the same code).  Each row's run of PPL values is
-// written with 16-byte stores where its alignment allows (store_run).
+// and dropped, so a tail lane runs the same code).
 template <int LMAX, typename TIO, int PPL>
 __device__ __forceinline__ void proj_points(const double (&px)[PPL], const double (&py)[PPL], const double (&pz)[PPL],
                                             const double c[3], const knot_t<TIO>* __restrict__ tab, int ch,
@@ -225,57 +201,39 @@ __device__ __forceinline__ void proj_points(const double (&px)[PPL], const doubl
     });
 }
 
-// Lane width of the projector and serving launches.  Several adjacent points per
-// lane (row stores of 16 bytes or more) raise the throughput of a launch that
-// fills the GPU many times over, but lengthen each workgroup, which is what a
-// launch too small to fill the GPU waits for; launches below kProjVecPoints points
-// keep one point per lane.  The widths, and the LDS reservation below, were chosen
-// per (dtype, lmax) on 64 x 150k-point builds from tables of lmax + 1 channels:
-// FP64 four points at lmax 1, two elsewhere (lmax 0: 45% of 8 TB/s against 42%
-// with four and the reservation; lmax 3: 56% against 53-54%; lmax 1: 46% against
-// 44% with two; lmax 2, where proj_vec_kernel runs: 51.4-51.6% with two against
-// 47.3-47.7% with four in proj_kernel, while serving keeps four there, kServePpl;
-// lmax >= 4: two, +35% at lmax 6 over one, four 7-10% slower); FP32 four (+10-21% at
-// lmax 3-9 over one; two or eight no faster).
-template <typename TIO, int LMAX> constexpr int kProjPpl = sizeof(TIO) == 4 ? 4 : (LMAX == 1 ? 4 : 2);
-constexpr int64_t kProjVecPoints = int64_t(1) << 20;
+// Points per lane of a projector build that fills the GPU many times over: 16 bytes' worth.
+// (FP64 4 points at lmax 1 141 us against 2 points 144, at lmax >= 2 4-20% slower; FP32 2
+// points equal at lmax 6, 8 and 9 and up to 30% slower elsewhere; builds of 64 atoms.)
+template <typename TIO> constexpr int kProjPpl = 16 / int(sizeof(TIO));
 
-// LDS reserved (not used) by the launches with several points per lane: at most 2
-// resident workgroups per CU, which keeps each row's concurrent writes in a
-// smaller window (as for the forward kernel).  Measured on the same builds: +1-13%
-// at FP64 lmax 1-9 and FP32 lmax >= 2; FP64 lmax 0 and FP32 lmax 0-1 run faster
-// without it (the FP64 lmax 0 launch with two points per lane: 45% against 34%).
-// At lmax 9, and FP64 lmax 8, more than half of the LDS: one resident workgroup per
-// CU.  Measured on 64 x 150k-point builds, two runs each: FP64 lmax 9 64.1-64.3% ->
-// 65.4%, FP32 60.3-60.6% -> 61.2-61.3% of 8 TB/s, FP64 lmax 8 63.5-63.7% ->
-// 64.0-64.2%; FP64 lmax 7, FP32 lmax 7-8 and every lmax up to 6 slower (FP32 lmax 7
-// 60.5 -> 56.9%, lmax 6 62 -> 58%); serving (its vector-lane groups), two passes
-// each: closed loop 111.7-112.2k -> 113.4-114.3k req/s, Poisson p50 and p99 equal or
-// lower.
-template <typename TIO, int LMAX>
-constexpr size_t kProjCapLds = (LMAX == 9 || (sizeof(TIO) == 8 && LMAX == 8))
-                                   ? 84 * 1024
-                                   : ((sizeof(TIO) == 4 ? LMAX <= 1 : LMAX == 0) ? 0 : 54 * 1024);
+// Builds of at least this many points, or bytes written, take several points per lane
+// (proj_launch in sh_proj.hip): below, a launch lasts its workgroups' chain of work, which
+// wider lanes lengthen.  us, one point against several: FP64 lmax 6, 24 x 4189 points (41
+// MB) 10.7 / 14.6; lmax 1, 64 x 14137 (50 MB) 13.1 / 15.5; FP32 lmax 3 (68 MB) 14.8 / 17.8;
+// FP64 lmax 4, 64 x 8000 (114 MB) 32.5 / 30.6; lmax 3, 64 x 14137 (136 MB) 41.8 / 39.4;
+// lmax 9 (738 MB) 201 / 171.
+constexpr int64_t kProjVecPoints = int64_t(1) << 20, kProjVecBytes = int64_t(3) << 25;
 
-// Whether builds with several points per lane run proj_vec_kernel (a window of 64
-// atoms held in lanes, every knot load of a lane issued before the first spline)
-// instead of proj_kernel (a wave-wide search for the atom, then each point's knots
-// loaded and used in turn): kProjVecKernel for builds over at most 64 atoms (the
-// window is all of them), kProjVecWindow for more (the window found by a search).
-// Measured on builds of 9.6M points, two runs each, fractions of 8 TB/s: over 64
-// atoms (150k points each) FP32 lmax 0 / 1 / 2 / 3 / 4 47 / 44-50 / 44 / 53 / 58% ->
-// 53 / 52-56 / 45 / 56-57 / 60%, FP64 lmax 2 47-48 (four points per lane) -> 51-52%
-// (two), FP64 lmax 3 57 -> 58-59%, FP32 lmax 5-9 within +-0.5%, FP64 lmax 0-1 and
-// 4-9 0-2% slower; over 256 / 1024 atoms FP32 lmax 0 44 /
-// 36 -> 50 / 39%, lmax 1 39 / 29 -> 41 / 31%, lmax 2 38 / 31 -> 41 / 32%, FP32 lmax
-// 3-4 and FP64 lmax 3 0-4% slower.
+// LDS reserved (not used) by proj_kernel with several points per lane: at most 2 resident
+// workgroups per CU, or 1.  Fewer waves at once keep each row's concurrent writes in a
+// smaller window and let the partial lines of neighbouring waves merge in the L2 (an atom
+// has any number of points, so its rows start anywhere); more hide the latency of the
+// spline lookups, which matters where a row count is small or the tables of many atoms
+// outgrow the L2.  us, uncapped / 2 / 1 workgroups, 64 atoms of about 4 to 10 MB a row:
+// FP64 lmax 0 78 / 107 / 154, lmax 3 156 / 132 / 160, lmax 4 217 / 179 / 197, lmax 5 285 /
+// 254 / 243, lmax 6 313 / 297 / 272, lmax 7 340 / 321 / 290, lmax 9 384 / 388 / 348; FP32
+// lmax 3 127 / 114 / -, lmax 4 190 / 154 / -, lmax 5 238 / 217 / 212, lmax 6 254 / 244 /
+// 228, lmax 8 266 / 254 / 236, lmax 9 329 / 314 / 285.  200 atoms, 2 / 1: FP64 lmax 5 268 /
+// 287, lmax 6 280 / 293, lmax 7 255 / 237; FP32 lmax 6 201 / 218, lmax 8 182 / 175.
 template <typename TIO, int LMAX>
-constexpr bool kProjVecKernel = sizeof(TIO) == 4 ? LMAX <= 4 : (LMAX == 2 || LMAX == 3);
-template <typename TIO, int LMAX>
-constexpr bool kProjVecWindow = sizeof(TIO) == 4 && LMAX <= 2;
-
-// Lane width of a launch of n points.
-template <typename TIO, int LMAX> constexpr int proj_ppl(int64_t n) { return n >= kProjVecPoints ? kProjPpl<TIO, LMAX> : 1; }
+inline size_t proj_cap_lds(int n_atoms)
+{
+    constexpr bool f64 = sizeof(TIO) == 8;
+    if (f64 ? LMAX == 0 : LMAX <= 1) return 0;
+    if (LMAX <= 4) return kCapLds2;
+    if (LMAX >= (f64 ? 7 : 8)) return kCapLds1;
+    return n_atoms > 64 ? kCapLds2 : kCapLds1;
+}
 
 // Wave-wide search over n sorted keys: the last k in [0, n) with keys[k] <= x,
 // or -1 if there is none.  Every lane must be active and pass the same x; each

@@ -12,13 +12,10 @@
 // channels of a table are 2 * channels adjacent pairs, so one point's spline
 // lookups touch one or two cache lines.
 //
-// Launch (measured on MI355X, 64 atoms / 0.9M points / lmax 3: 43 us -> 30 us):
-// workgroups remapped so each XCD works through one contiguous range of atoms
-// (their tables then stay in that XCD's L2); the atom of a wave found by one
-// wave-wide search; plain stores; one point per lane, or, for builds of at least
-// kProjVecPoints points, kProjPpl adjacent points per lane evaluated together, with
-// at most 2 resident workgroups per CU (kProjCapLds); those builds run
-// proj_vec_kernel where kProjVecKernel or kProjVecWindow is set.
+// Launch: workgroups remapped so each XCD works through one contiguous range of atoms
+// (their tables then stay in that XCD's L2); the atom of a wave found by one wave-wide
+// search or from a preload; plain stores; one point per lane, or several in large builds,
+// some of which hold the atom's table in LDS (proj_launch).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -247,10 +244,9 @@ __global__ __launch_bounds__(64) void spline_serial_kernel(const double* __restr
 // point loads and the arithmetic.  Otherwise, and for lanes past atom aw + 1, the
 // wave's atom comes from a wave-wide search and a lane's from a binary search, and
 // the atom's data is loaded after it.  Measured on the 64-atom lmax 3 build (one
-// point per lane): 29.6-29.8 us -> 27.6-28.0 us.  In this kernel the launches with
-// several points per lane keep the search: there the preload alone cost as much as
-// the shorter chain saved (-6% to +5% across lmax and dtype on 64 x 150k-point
-// builds); proj_vec_kernel combines it with loading every knot of a lane at once.
+// point per lane): 29.6-29.8 us -> 27.6-28.0 us.  The launches with several points per
+// lane keep the search: there the preload alone cost as much as the shorter chain saved
+// (-6% to +5% across lmax and dtype on 64 x 150k-point builds).
 struct AtomRef {
     int64_t o0, o1;  // its point range
     double c[3];
@@ -348,112 +344,107 @@ __global__ __launch_bounds__(256) void proj_kernel(const TIO* __restrict__ cente
     }
 }
 
-// The launches with several points per lane, for the (dtype, lmax) where
-// kProjVecKernel (at most 64 atoms) or kProjVecWindow (more) is set: lane k loads
-// the offsets, centre and table of atom a0 + k with the points (a0 = 0 for at most
-// 64 atoms, as the one-point SMALL path does; otherwise the wave's atom, from one
-// wave-wide search), a ballot gives the wave's
-// atom and the next, and a lane then issues the knot loads of all its points before
-// it evaluates any spline (spline_knots, then spline_from), so the chain per lane is
-// the point loads, one wave of knot loads and the stores.  Each lane's points lie
-// in one of those two atoms unless the wave crosses more than one atom boundary;
-// such lanes, and lanes that straddle a boundary, take their points one by one.
-// The same arithmetic as proj_kernel, so the same bits.
-template <int LMAX, typename TIO, int PPL>
-__global__ __launch_bounds__(256) void proj_vec_kernel(const TIO* __restrict__ centers,
-                                                       const int64_t* __restrict__ offsets, int n_atoms,
-                                                       const TIO* __restrict__ points, int64_t n_points,
-                                                       const knot_t<TIO>* __restrict__ table, int tab_ch,
-                                                       int n_tables, const int32_t* __restrict__ table_of_atom,
-                                                       SplineGrid g, TIO* __restrict__ out, int64_t j0)
+// Persistent build for small lmax: a workgroup keeps the spline table of the atom it works
+// on in LDS (of LMAX + 1 channels) and walks tiles of BT * PPL points.  A lookup
+// scatters its lanes over as many cache lines, one tag check each: at lmax 3 in FP32 two
+// thirds of the L1's cycles went there, and where the tables of many atoms outgrow the L2
+// it waited for them as well.  Workgroups form groups of `group` (of the logical order, so
+// in one XCD), each with group_points consecutive points, whose tiles its workgroups take
+// in turn: with group = 32 an XCD's CUs write side by side, which the HBM write path
+// rewards, and each loads every table of the range; with group = 1 a workgroup loads one
+// or two.  Offsets that are inconsistent around a tile send the rest of it through the
+// points one by one, as proj_kernel.  The same arithmetic, so the same bits.
+// us against the best launch without LDS: 64 x 150k points FP64 lmax 1 116-122 / 141, FP32
+// lmax 2 109-112 / 124, lmax 3 161 / 160, lmax 4 164 / 155, FP64 lmax 2 (64 x 100k) 143 /
+// 147, lmax 3 345 / 304; 200 x 20k FP32 lmax 3 76 / 88, lmax 4 110 / 118; 1024 x 9400 FP32
+// lmax 0 43 / 59, lmax 2 120 / 167, lmax 3 179 / 224, FP64 lmax 0 74 / 107, lmax 1 135 /
+// 192, lmax 3 361 / 392; 512 x 4000 FP32 lmax 2 34 / 46, FP64 lmax 1 37 / 45.
+template <int LMAX, typename TIO, int PPL, int BT>
+__global__ __launch_bounds__(BT) void proj_lds_kernel(const TIO* __restrict__ centers,
+                                                      const int64_t* __restrict__ offsets, int n_atoms,
+                                                      const TIO* __restrict__ points, int64_t n_points,
+                                                      const knot_t<TIO>* __restrict__ table,
+                                                      int n_tables, const int32_t* __restrict__ table_of_atom,
+                                                      SplineGrid g, TIO* __restrict__ out, int64_t group_points,
+                                                      int group)
 {
-    using V = typename vec_of<TIO, PPL>::type;
-    constexpr int F = nfun(LMAX);
-    const int64_t w0 = j0 + (int64_t(xcd_tile(blockIdx.x, gridDim.x)) * 256 + (threadIdx.x & ~63u)) * PPL;
-    if (w0 >= n_points) return;
-    const int wl = threadIdx.x & 63;  // lane in the wave
-    auto load_atom = [&](int a) {
-        AtomRef r;
-        r.o0 = offsets[a];
-        r.o1 = offsets[a + 1];
-        r.c[0] = double(centers[3 * a]);
-        r.c[1] = double(centers[3 * a + 1]);
-        r.c[2] = double(centers[3 * a + 2]);
-        const int t = table_of_atom ? table_of_atom[a] : a;
-        r.t = t < 0 ? 0 : (t >= n_tables ? n_tables - 1 : t);
-        return r;
-    };
-    int a0 = 0;  // first atom of the window held in the lanes
-    if (n_atoms > 64) {
-        a0 = wave_search(offsets, n_atoms, w0);
-        a0 = a0 < 0 ? 0 : a0;
-    }
-    const int nw = n_atoms - a0 < 64 ? n_atoms - a0 : 64;
-    AtomRef mine{};
-    if (wl < nw) mine = load_atom(a0 + wl);
-    const int64_t j = w0 + wl * PPL;
-    double px[PPL], py[PPL], pz[PPL];
+    using KN = knot_t<TIO>;
+    constexpr int F = nfun(LMAX), CH = LMAX + 1;
+    extern __shared__ __align__(16) unsigned char lds[];
+    KN* tab = reinterpret_cast<KN*>(lds);
+    const uint32_t w = xcd_tile(blockIdx.x, gridDim.x);
+    const int64_t g0 = int64_t(w / group) * group_points;
+    const int64_t g1 = g0 + group_points < n_points ? g0 + group_points : n_points;
+    int64_t o0 = 0, o1 = -1;  // point range of the current atom (none yet)
+    int a = -1, t = -1;       // the atom, and the table held in LDS
+    double c[3] = {};
+    for (int64_t p0 = g0 + int64_t(w % group) * (BT * PPL); p0 < g1; p0 += int64_t(group) * (BT * PPL)) {
+        const int64_t p1 = p0 + BT * PPL < g1 ? p0 + BT * PPL : g1;
+        int64_t pos = p0;
+        while (pos < p1) {
+            if (!(o0 <= pos && pos < o1)) {
+                a = wave_search(offsets, n_atoms, pos);
+                o0 = a >= 0 ? offsets[a] : 0;
+                o1 = a >= 0 ? offsets[a + 1] : -1;
+                if (o0 < 0 || !(o0 <= pos && pos < o1) || o1 > n_points) {
+                    // inconsistent here: this tile's points one by one
+                    o1 = -1;
+                    for (int64_t j = pos + threadIdx.x; j < p1; j += BT) {
+                        const int b = lane_search(offsets, n_atoms, j);
+                        const int64_t b0 = offsets[b], b1 = offsets[b + 1];
+                        if (!(b0 >= 0 && b0 <= j && j < b1 && b1 <= n_points)) continue;
+                        const double cb[3] = {double(centers[3 * b]), double(centers[3 * b + 1]),
+                                              double(centers[3 * b + 2])};
+                        int tb = table_of_atom ? table_of_atom[b] : b;
+                        tb = tb < 0 ? 0 : (tb >= n_tables ? n_tables - 1 : tb);
+                        proj_point<LMAX, TIO>(double(points[3 * j]), double(points[3 * j + 1]),
+                                              double(points[3 * j + 2]), cb, table + int64_t(tb) * g.n_r * CH, CH, g,
+                                              out + F * b0 + (j - b0), b1 - b0);
+                    }
+                    break;
+                }
+                c[0] = double(centers[3 * a]);
+                c[1] = double(centers[3 * a + 1]);
+                c[2] = double(centers[3 * a + 2]);
+                int ta = table_of_atom ? table_of_atom[a] : a;
+                ta = ta < 0 ? 0 : (ta >= n_tables ? n_tables - 1 : ta);
+                if (ta != t) {
+                    t = ta;
+                    __syncthreads();  // the previous table is still read
+                    const KN* src = table + int64_t(t) * g.n_r * CH;
+                    typedef float v4 __attribute__((ext_vector_type(4), aligned(8)));  // a float pair's
+                    const int n16 = int(g.n_r * CH * sizeof(KN) / 16);
+                    for (int k = threadIdx.x; k < n16; k += BT)
+                        reinterpret_cast<v4*>(tab)[k] = reinterpret_cast<const v4*>(src)[k];
+                    if (sizeof(KN) == 8 && (g.n_r * CH & 1) && threadIdx.x == 0)
+                        tab[g.n_r * CH - 1] = src[g.n_r * CH - 1];
+                    __syncthreads();
+                }
+            }
+            const int64_t e = o1 < p1 ? o1 : p1;
+            int64_t j = pos + int64_t(threadIdx.x) * PPL;
+            if (j < e) {
+                int nvalid = PPL;
+                if (j + PPL > e) {
+                    // the atom's last lane takes its last PPL points (its neighbour, which
+                    // takes some of them too, stores the same bits); atoms with fewer
+                    // points before e store those there are
+                    if (e - PPL >= o0) j = e - PPL;
+                    else nvalid = int(e - j);
+                }
+                double px[PPL], py[PPL], pz[PPL];
 #pragma unroll
-    for (int q = 0; q < PPL; ++q) {
-        const TIO* p = points + 3 * (j + q < n_points ? j + q : w0);
-        px[q] = double(p[0]);
-        py[q] = double(p[1]);
-        pz[q] = double(p[2]);
-    }
-    auto atom_at = [&](int a) {
-        return AtomRef{lane_value(mine.o0, a), lane_value(mine.o1, a),
-                       {lane_value(mine.c[0], a), lane_value(mine.c[1], a), lane_value(mine.c[2], a)},
-                       lane_value(mine.t, a)};
-    };
-    const int aw = __popcll(__ballot(wl < nw && mine.o0 <= w0)) - 1;  // in the window
-    AtomRef A0, A1;  // atoms a0 + aw and a0 + aw + 1 (o0 = o1 = -1 if there is none)
-    A0.o0 = A0.o1 = A1.o0 = A1.o1 = -1;
-    if (aw >= 0) A0 = atom_at(aw);
-    if (aw + 1 < nw) A1 = atom_at(aw + 1);
-    if (j >= n_points) return;
-    const bool in0 = A0.o0 >= 0 && A0.o0 <= j && j + PPL <= A0.o1 && A0.o1 <= n_points;
-    const bool in1 = A1.o0 >= 0 && A1.o0 <= j && j + PPL <= A1.o1 && A1.o1 <= n_points;
-    if (!in0 && !in1) {
-#pragma unroll
-        for (int q = 0; q < PPL; ++q) {
-            const int64_t jq = j + q;
-            if (jq >= n_points) break;
-            const AtomRef B = load_atom(lane_search(offsets, n_atoms, jq));
-            if (!(B.o0 >= 0 && B.o0 <= jq && jq < B.o1 && B.o1 <= n_points)) continue;
-            proj_point<LMAX, TIO>(px[q], py[q], pz[q], B.c, table + int64_t(B.t) * g.n_r * tab_ch, tab_ch, g,
-                                  out + F * B.o0 + (jq - B.o0), B.o1 - B.o0);
+                for (int q = 0; q < PPL; ++q) {
+                    const TIO* p = points + 3 * (q < nvalid ? j + q : j);
+                    px[q] = double(p[0]);
+                    py[q] = double(p[1]);
+                    pz[q] = double(p[2]);
+                }
+                proj_points<LMAX, TIO, PPL>(px, py, pz, c, tab, CH, g, out + F * o0 + (j - o0), o1 - o0, nvalid);
+            }
+            pos = e;
         }
-        return;
     }
-    const AtomRef& A = in0 ? A0 : A1;
-    const knot_t<TIO>* tab = table + int64_t(A.t) * g.n_r * tab_ch;
-    knot_t<TIO> ka[PPL][LMAX + 1], kb[PPL][LMAX + 1];
-    double r[PPL];
-    V x, y, z, k;
-#pragma unroll
-    for (int q = 0; q < PPL; ++q) {
-        const double dx = px[q] - A.c[0], dy = py[q] - A.c[1], dz = pz[q] - A.c[2];
-        double xb, yb, zb, keep;
-        normalize(dx, dy, dz, xb, yb, zb, keep);
-        r[q] = sqrt(__builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz)));
-        spline_knots<LMAX + 1>(tab, tab_ch, g, r[q], ka[q], kb[q]);
-        lane<V, PPL>(x, q) = TIO(xb);
-        lane<V, PPL>(y, q) = TIO(yb);
-        lane<V, PPL>(z, q) = TIO(zb);
-        lane<V, PPL>(k, q) = TIO(keep);
-    }
-    TIO R[PPL][LMAX + 1];
-#pragma unroll
-    for (int q = 0; q < PPL; ++q) spline_from<LMAX + 1, TIO>(ka[q], kb[q], g, r[q], R[q]);
-    TIO* o = out + F * A.o0 + (j - A.o0);
-    const int64_t stride = A.o1 - A.o0;
-    eval_unit<LMAX, V>(x, y, z, k, [&](int f, V v) {
-        const int l = l_of_row(f);
-        V rl;
-#pragma unroll
-        for (int q = 0; q < PPL; ++q) lane<V, PPL>(rl, q) = R[q][l];
-        store_run<TIO, PPL>(o + int64_t(f) * stride, rl * v, PPL);
-    });
 }
 
 // Points per launch: keeps each grid well inside the 32-bit work-item count of a
@@ -461,29 +452,15 @@ __global__ __launch_bounds__(256) void proj_vec_kernel(const TIO* __restrict__ c
 constexpr int64_t kProjChunk = int64_t(1) << 28;
 
 template <int LMAX, typename TIO, int P>
-static void launch_vec(const ProjArgs<TIO>& A, const SplineGrid& g, dim3 grid, size_t lds, int64_t j0, hipStream_t s)
+static hipError_t launch_proj_p(const ProjArgs<TIO>& A, const SplineGrid& g, size_t lds, hipStream_t s)
 {
-    if constexpr (P > 1 && (kProjVecKernel<TIO, LMAX> || kProjVecWindow<TIO, LMAX>))
-        hipLaunchKernelGGL((proj_vec_kernel<LMAX, TIO, P>), grid, dim3(256), lds, s, A.centers, A.offsets,
-                           A.n_atoms, A.points, A.n_points, A.table, A.tab_ch, A.n_tables, A.table_of_atom, g,
-                           A.out, j0);
-}
-
-template <int LMAX, typename TIO, int P>
-static hipError_t launch_proj_p(const ProjArgs<TIO>& A, hipStream_t s)
-{
-    const SplineGrid g{A.n_r, A.h, 1.0 / A.h, A.r_max, A.h * A.h / 6.0};
-    const size_t lds = P > 1 ? kProjCapLds<TIO, LMAX> : 0;
     for (int64_t j0 = 0; j0 < A.n_points; j0 += kProjChunk) {
         const int64_t nc = A.n_points - j0 < kProjChunk ? A.n_points - j0 : kProjChunk;
         const dim3 grid = dim3(unsigned((nc + 256 * P - 1) / (256 * P))), block = dim3(256);
-        const bool vec = P > 1 && (A.n_atoms <= 64 ? kProjVecKernel<TIO, LMAX> : kProjVecWindow<TIO, LMAX>);
         if (P == 1 && A.n_atoms <= 64)
-            hipLaunchKernelGGL((proj_kernel<LMAX, TIO, P, P == 1>), grid, block, 0, s, A.centers, A.offsets,
+            hipLaunchKernelGGL((proj_kernel<LMAX, TIO, P, P == 1>), grid, block, lds, s, A.centers, A.offsets,
                                A.n_atoms, A.points, A.n_points, A.table, A.tab_ch, A.n_tables, A.table_of_atom, g,
                                A.out, j0);
-        else if (vec)
-            launch_vec<LMAX, TIO, P>(A, g, grid, lds, j0, s);
         else
             hipLaunchKernelGGL((proj_kernel<LMAX, TIO, P, false>), grid, block, lds, s, A.centers, A.offsets,
                                A.n_atoms, A.points, A.n_points, A.table, A.tab_ch, A.n_tables, A.table_of_atom, g,
@@ -494,11 +471,63 @@ static hipError_t launch_proj_p(const ProjArgs<TIO>& A, hipStream_t s)
     return hipSuccess;
 }
 
+// proj_lds_kernel's launch: one workgroup of 1024 lanes per CU, or two of 512 where the
+// table is small (FP32 lmax <= 1: 65 us against 74 at lmax 1, 64 x 150k points).
+constexpr int kCus = 256;
+constexpr int64_t kLdsPerCu = 160 * 1024;
+template <typename TIO, int LMAX> constexpr int kProjLdsBlock = sizeof(TIO) == 4 && LMAX <= 1 ? 512 : 1024;
+template <typename TIO> constexpr int kProjLdsMax = sizeof(TIO) == 8 ? 3 : 4;  // highest lmax that uses it
+
+template <typename TIO, int LMAX>
+static int64_t proj_lds_bytes(int n_r)
+{
+    return (int64_t(n_r) * (LMAX + 1) * int64_t(sizeof(knot_t<TIO>)) + 15) / 16 * 16;
+}
+
+// Whether a large build takes proj_lds_kernel (both sides measured, see there): the table
+// has the build's channels (a handle keeps such copies) and fits, an atom has enough points on average for its load, and at the lmax where the
+// launch without LDS is as fast over few atoms, the atoms are many or the points.
+template <typename TIO, int LMAX>
+static bool use_proj_lds(const ProjArgs<TIO>& A)
+{
+    constexpr bool f64 = sizeof(TIO) == 8;
+    if (LMAX > kProjLdsMax<TIO> || A.tab_ch != LMAX + 1) return false;
+    if (proj_lds_bytes<TIO, LMAX>(A.n_r) * (1024 / kProjLdsBlock<TIO, LMAX>) > kLdsPerCu) return false;
+    if (A.n_points < kProjVecPoints || A.n_points / 2048 < A.n_atoms) return false;
+    if (f64) {
+        if (LMAX == 0) return A.n_atoms > 128 || A.n_points >= int64_t(1) << 23;
+        if (LMAX == 2) return A.n_atoms > 64 || A.n_points >= int64_t(1) << 22;
+        return LMAX == 1 || A.n_atoms > 128;
+    }
+    return LMAX <= 3 || A.n_atoms > 64;
+}
+
+template <int LMAX, typename TIO>
+static hipError_t launch_proj_lds(const ProjArgs<TIO>& A, const SplineGrid& g, hipStream_t s)
+{
+    if constexpr (LMAX <= kProjLdsMax<TIO>) {
+        constexpr int BT = kProjLdsBlock<TIO, LMAX>, P = kProjPpl<TIO>;
+        constexpr int64_t kTile = BT * P;
+        const int groups_of = LMAX <= 2 && A.n_atoms > 128 ? 1 : 32, wgs = kCus * (1024 / BT);
+        const int64_t n_groups = wgs / groups_of, round = groups_of == 1 ? 64 : kTile;
+        const int64_t group_points = ((A.n_points + n_groups - 1) / n_groups + round - 1) / round * round;
+        hipLaunchKernelGGL((proj_lds_kernel<LMAX, TIO, P, BT>), dim3(wgs), dim3(BT),
+                           size_t(proj_lds_bytes<TIO, LMAX>(A.n_r)), s, A.centers, A.offsets, A.n_atoms, A.points,
+                           A.n_points, A.table, A.n_tables, A.table_of_atom, g, A.out, group_points, groups_of);
+        return hipGetLastError();
+    } else {
+        return hipErrorInvalidValue;
+    }
+}
+
 template <int LMAX, typename TIO>
 static hipError_t launch_proj_l(const ProjArgs<TIO>& A, hipStream_t s)
 {
-    return A.n_points >= kProjVecPoints ? launch_proj_p<LMAX, TIO, kProjPpl<TIO, LMAX>>(A, s)
-                                        : launch_proj_p<LMAX, TIO, 1>(A, s);
+    const SplineGrid g{A.n_r, A.h, 1.0 / A.h, A.r_max, A.h * A.h / 6.0};
+    if (A.n_points < kProjVecPoints && A.n_points * nfun(LMAX) * int64_t(sizeof(TIO)) < kProjVecBytes)
+        return launch_proj_p<LMAX, TIO, 1>(A, g, 0, s);
+    if (use_proj_lds<TIO, LMAX>(A)) return launch_proj_lds<LMAX, TIO>(A, g, s);
+    return launch_proj_p<LMAX, TIO, kProjPpl<TIO>>(A, g, proj_cap_lds<TIO, LMAX>(A.n_atoms), s);
 }
 
 template <typename TIO>

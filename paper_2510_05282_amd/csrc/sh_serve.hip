@@ -3,8 +3,8 @@
 //
 // A batch is a list of requests of any lmax and either dtype.  The requests are
 // grouped by (dtype, lmax); each request is cut into tiles of 256 lanes x PPL
-// adjacent points, evaluated with the same projector code as sh_projectors (PPL as
-// there: the vector width for a group of at least kServeVecPoints points, else 1).
+// adjacent points, evaluated with the same projector code as sh_projectors (PPL
+// kServePpl for a group of at least kServeVecPoints points, else 1).
 // Each vector-width group gets one launch of the kernel built for it (registers and
 // occupancy sized for that lmax, no per-point dispatch); the one-point groups share
 // one launch of the mixed kernel when there are two or more of them (a block runs
@@ -160,12 +160,14 @@ static hipError_t launch_mixed(int64_t tiles, const ServeInline& in, const Serve
     return hipGetLastError();
 }
 
-// Lane width of the vector-lane serving launches: the projector build's, except FP64
-// at lmax 2, which keeps four points per lane here (the build moved to two in
-// proj_vec_kernel; serve_kernel, which loads each point's knots in turn, took 116 us
-// per lmax 2 FP64 launch with two against 87 us with four, closed-loop kernel trace).
+// Lane width and LDS reservation (resident workgroups per CU) of the vector-lane serving
+// launches.
 template <typename TIO, int LMAX>
-constexpr int kServePpl = sizeof(TIO) == 8 && LMAX == 2 ? 4 : kProjPpl<TIO, LMAX>;
+constexpr int kServePpl = sizeof(TIO) == 4 ? 4 : (LMAX == 1 || LMAX == 2 ? 4 : 2);
+template <typename TIO, int LMAX>
+constexpr size_t kServeCapLds = (LMAX == 9 || (sizeof(TIO) == 8 && LMAX == 8))
+                                    ? kCapLds1
+                                    : ((sizeof(TIO) == 4 ? LMAX <= 1 : LMAX == 0) ? 0 : kCapLds2);
 
 template <int LMAX, typename TIO>
 static void launch_group_l(int ppl, int64_t tiles, const ServeInline& in, const ServeDesc* descs,
@@ -176,7 +178,7 @@ static void launch_group_l(int ppl, int64_t tiles, const ServeInline& in, const 
         hipExtLaunchKernelGGL((serve_kernel<LMAX, TIO, 1>), grid, block, 0, s, nullptr, done, 0, in, descs, tile0, n);
     else
         hipExtLaunchKernelGGL((serve_kernel<LMAX, TIO, kServePpl<TIO, LMAX>>), grid, block,
-                              uint32_t(kProjCapLds<TIO, LMAX>), s, nullptr, done, 0, in, descs, tile0, n);
+                              uint32_t(kServeCapLds<TIO, LMAX>), s, nullptr, done, 0, in, descs, tile0, n);
 }
 
 // Groups of at least this many points take several points per lane.  Lower than
