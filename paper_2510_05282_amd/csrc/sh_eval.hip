@@ -52,9 +52,15 @@ static hipError_t launch_one(Inputs<MODE, TIO> in, TIO* out, int64_t n, int64_t 
 template <int LMAX, typename TIO, In MODE>
 static hipError_t launch_fwd_l(int64_t n, Inputs<MODE, TIO> in, TIO* out, int64_t ld, hipStream_t s)
 {
-    constexpr int kVec = LMAX == 1 ? 1 : 16 / sizeof(TIO);  // store_shape never asks lmax 1 for more
-    const StoreShape f = store_shape<nfun(LMAX), TIO>(n * nfun(LMAX) * int64_t(sizeof(TIO)),
-                                                      on_lines(out, ld * sizeof(TIO)));
+    // store_shape never asks lmax 1 for more than one point per lane
+    constexpr bool kBusy = MODE == In::kAngles && LMAX <= 6;
+    constexpr int kVec = LMAX == 1 && !kBusy ? 1 : 16 / sizeof(TIO);
+    StoreShape f = store_shape<nfun(LMAX), TIO>(n * nfun(LMAX) * int64_t(sizeof(TIO)), on_lines(out, ld * sizeof(TIO)));
+    // angles take two FP64 sines and cosines per point, which at few rows need every wave
+    // (us, wide uncapped / capped / one point: FP64 lmax 2, 8000000 points 137 / 180 / 135; lmax 3,
+    // 1500000 43.4 / 48.0 / 45.6; FP32 lmax 1, 9000001 64 / 86 / 94; lmax 6, 1000001 43.4 /
+    // 45.9 / 52.4)
+    if (kBusy && n * nfun(LMAX) * int64_t(sizeof(TIO)) >= kWideBytes) f = {LMAX != 2 || sizeof(TIO) == 4, 0};
     for (int64_t c0 = 0; c0 < n; c0 += kChunk) {
         const int64_t nc = n - c0 < kChunk ? n - c0 : kChunk;
         const hipError_t e = f.wide && nc >= kVec
@@ -135,7 +141,8 @@ static hipError_t launch_complex_l(int64_t n, AnyInputs<TIO> in, TIO* out, int64
     constexpr int kRows = (SPINOR ? 4 : 1) * nfun(LMAX);
     constexpr int kVec = sizeof(TIO) == 4 && kRows != 4 ? 2 : 1;  // store_shape never asks 4 rows for more
     constexpr int64_t kValue = 2 * sizeof(TIO);
-    const StoreShape f = store_shape<kRows, TIO>(n * kRows * kValue, on_lines(out, ld * kValue));
+    StoreShape f = store_shape<kRows, TIO>(n * kRows * kValue, on_lines(out, ld * kValue));
+    if (in.mode == In::kAngles && kRows <= 16) f.lds = 0;  // as for the real harmonics of angles
     for (int64_t c0 = 0; c0 < n; c0 += kChunk) {
         const int64_t nc = n - c0 < kChunk ? n - c0 : kChunk;
         const hipError_t e = f.wide && nc >= kVec

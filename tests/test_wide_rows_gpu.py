@@ -91,3 +91,23 @@ def test_other_rows(dev, dtype, kind, lmax, more):
     y = fn(x)
     for i, p in _pieces(fn, x, n // 3 + 1):
         assert torch.equal(y[..., i:i + p.shape[-1]], p)
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("kind,lmax", [("real", 1), ("real", 2), ("real", 6), ("real", 7), ("complex", 1), ("complex", 3)])
+@pytest.mark.parametrize("more", [0, 1])
+def test_angle_rows(dev, dtype, kind, lmax, more):
+    per_point = (lmax + 1) ** 2 * (torch.finfo(dtype).bits // 8) * (1 if kind == "real" else 2)
+    n = -(-(1 << 27) // per_point) // 4 * 4 + 4 + more  # just over 2^27 bytes of output
+    print("case: wide rows of angles,", kind, "lmax", lmax, "n", n, dtype, flush=True)
+    g = torch.Generator(device=dev)
+    g.manual_seed(n)
+    a = torch.rand((2, n), generator=g, dtype=torch.float64, device=dev).mul_(3.1).to(dtype)
+    fn = {"real": sh.sh_eval_angles if dtype == torch.float64 else sh.sh_eval_angles_f32,
+          "complex": sh.sh_eval_complex_angles}[kind]
+    y = fn(lmax, a[0].contiguous(), a[1].contiguous())
+    m = n // 3 + 1
+    for i in range(0, n, m):
+        p = fn(lmax, a[0, i:i + m].contiguous(), a[1, i:i + m].contiguous())
+        assert torch.equal(torch.view_as_real(y[:, i:i + m]) if kind == "complex" else y[:, i:i + m],
+                           torch.view_as_real(p) if kind == "complex" else p)
