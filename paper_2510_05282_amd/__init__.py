@@ -42,9 +42,25 @@ def row(l: int, m: int) -> int:
     return l * l + l + m
 
 
+# What a call needs from torch besides its tensors: the stream's handle, and its device
+# to be the current one.  The handle comes as a number (building a Stream object takes 2-3
+# us of host time, a small call's launch 4), and the device is set only where it differs.
+_raw_stream = torch._C._cuda_getCurrentRawStream
+_current_device = torch._C._cuda_getDevice
+
+
 def _stream(dev: torch.device, stream) -> int:
-    s = torch.cuda.current_stream(dev) if stream is None else stream
-    return int(s.cuda_stream)
+    return _raw_stream(dev.index) if stream is None else int(stream.cuda_stream)
+
+
+def _call(fn: str, dev: torch.device, *args) -> None:
+    f = getattr(lib(), fn)
+    if dev.index == _current_device():
+        rc = f(*args)
+    else:
+        with torch.cuda.device(dev):
+            rc = f(*args)
+    check(fn, rc)
 
 
 def _points(xyz: torch.Tensor, dtype: torch.dtype) -> int:
@@ -76,9 +92,7 @@ def sh_eval_ld(lmax: int, xyz: torch.Tensor, out: torch.Tensor, stream=None) -> 
     if out.dim() != 2 or out.shape[0] != F or out.shape[1] != n or (n > 1 and out.stride(1) != 1):
         raise ValueError(f"out must be a [{F}, {n}] view with unit column stride")
     ld = out.stride(0) if F > 1 else max(n, 1)
-    with torch.cuda.device(xyz.device):
-        check("sh_eval_ld", lib().sh_eval_ld(lmax, n, xyz.data_ptr(), out.data_ptr(), ld, code,
-                                             _stream(xyz.device, stream)))
+    _call("sh_eval_ld", xyz.device, lmax, n, xyz.data_ptr(), out.data_ptr(), ld, code, _stream(xyz.device, stream))
     return out
 
 
@@ -90,9 +104,7 @@ def _eval(fn: str, dtype: torch.dtype, lmax: int, xyz: torch.Tensor, out, stream
     elif (out.dtype != dtype or out.device != xyz.device or tuple(out.shape) != (F, n)
           or not out.is_contiguous()):
         raise ValueError(f"out must be a contiguous [{F}, {n}] {dtype} tensor on {xyz.device}")
-    with torch.cuda.device(xyz.device):
-        check(fn, getattr(lib(), fn)(lmax, n, xyz.data_ptr(), out.data_ptr(),
-                                     _stream(xyz.device, stream)))
+    _call(fn, xyz.device, lmax, n, xyz.data_ptr(), out.data_ptr(), _stream(xyz.device, stream))
     return out
 
 
@@ -138,9 +150,7 @@ def _angles(fn, dtype, lmax, theta, phi, out, stream):
         out = torch.empty((F, n), dtype=dtype, device=theta.device)
     elif out.dtype != dtype or tuple(out.shape) != (F, n) or not out.is_contiguous():
         raise ValueError(f"out must be a contiguous [{F}, {n}] {dtype} tensor")
-    with torch.cuda.device(theta.device):
-        check(fn, getattr(lib(), fn)(lmax, n, theta.data_ptr(), phi.data_ptr(), out.data_ptr(),
-                                     _stream(theta.device, stream)))
+    _call(fn, theta.device, lmax, n, theta.data_ptr(), phi.data_ptr(), out.data_ptr(), _stream(theta.device, stream))
     return out
 
 
@@ -160,8 +170,7 @@ def _complex(fn, dtype, ctype, lmax, xyz, out, stream):
         out = torch.empty((F, n), dtype=ctype, device=xyz.device)
     elif out.dtype != ctype or tuple(out.shape) != (F, n) or not out.is_contiguous():
         raise ValueError(f"out must be a contiguous [{F}, {n}] {ctype} tensor")
-    with torch.cuda.device(xyz.device):
-        check(fn, getattr(lib(), fn)(lmax, n, xyz.data_ptr(), out.data_ptr(), _stream(xyz.device, stream)))
+    _call(fn, xyz.device, lmax, n, xyz.data_ptr(), out.data_ptr(), _stream(xyz.device, stream))
     return out
 
 
@@ -192,8 +201,7 @@ def _spinor(fn, dtype, ctype, lmax, xyz, out, stream):
         out = torch.empty((S, 2, n), dtype=ctype, device=xyz.device)
     elif out.dtype != ctype or tuple(out.shape) != (S, 2, n) or not out.is_contiguous():
         raise ValueError(f"out must be a contiguous [{S}, 2, {n}] {ctype} tensor")
-    with torch.cuda.device(xyz.device):
-        check(fn, getattr(lib(), fn)(lmax, n, xyz.data_ptr(), out.data_ptr(), _stream(xyz.device, stream)))
+    _call(fn, xyz.device, lmax, n, xyz.data_ptr(), out.data_ptr(), _stream(xyz.device, stream))
     return out
 
 
@@ -228,10 +236,8 @@ def _cplx_in(fn: str, spinor: bool, lmax: int, input_kind: int, a: torch.Tensor,
         out = torch.empty(shape, dtype=ctype, device=a.device)
     elif out.dtype != ctype or tuple(out.shape) != shape or not out.is_contiguous():
         raise ValueError(f"out must be a contiguous {list(shape)} {ctype} tensor")
-    with torch.cuda.device(a.device):
-        check(fn, getattr(lib(), fn)(lmax, n, input_kind, code, a.data_ptr(),
-                                     b.data_ptr() if input_kind == SH_IN_ANGLES else None, out.data_ptr(),
-                                     _stream(a.device, stream)))
+    _call(fn, a.device, lmax, n, input_kind, code, a.data_ptr(), b.data_ptr() if input_kind == SH_IN_ANGLES else None,
+          out.data_ptr(), _stream(a.device, stream))
     return out
 
 
@@ -279,9 +285,8 @@ def _grad(fn: str, dtype, lmax, xyz, grad_out, grad_xyz, stream):
     elif (grad_xyz.dtype != dtype or grad_xyz.device != xyz.device
           or tuple(grad_xyz.shape) != (n, 3) or not grad_xyz.is_contiguous()):
         raise ValueError(f"grad_xyz must be a contiguous [{n}, 3] {dtype} tensor on {xyz.device}")
-    with torch.cuda.device(xyz.device):
-        check(fn, getattr(lib(), fn)(lmax, n, xyz.data_ptr(), grad_out.data_ptr(), grad_xyz.data_ptr(),
-                                     _stream(xyz.device, stream)))
+    _call(fn, xyz.device, lmax, n, xyz.data_ptr(), grad_out.data_ptr(), grad_xyz.data_ptr(),
+          _stream(xyz.device, stream))
     return grad_xyz
 
 
@@ -311,9 +316,8 @@ def sh_eval_jac(lmax: int, xyz: torch.Tensor, out: torch.Tensor | None = None,
         if (t.dtype != torch.float64 or t.device != xyz.device or tuple(t.shape) != shape
                 or not t.is_contiguous()):
             raise ValueError(f"{name} must be a contiguous {list(shape)} float64 tensor on {xyz.device}")
-    with torch.cuda.device(xyz.device):
-        check("sh_eval_jac", lib().sh_eval_jac(lmax, n, xyz.data_ptr(), out.data_ptr(), jac.data_ptr(),
-                                               _stream(xyz.device, stream)))
+    _call("sh_eval_jac", xyz.device, lmax, n, xyz.data_ptr(), out.data_ptr(), jac.data_ptr(),
+          _stream(xyz.device, stream))
     return out, jac
 
 
@@ -417,10 +421,8 @@ def _projectors(fn: str, dtype, lmax, centers, offsets, points, radial, table_of
                 or tuple(table_of_atom.shape) != (n_atoms,) or not table_of_atom.is_contiguous()):
             raise ValueError("table_of_atom must be a contiguous int32 CUDA tensor of n_atoms entries")
         toa = table_of_atom.data_ptr()
-    with torch.cuda.device(points.device):
-        check(fn, getattr(lib(), fn)(lmax, n_atoms, centers.data_ptr(), offsets.data_ptr(), n_points,
-                                     points.data_ptr(), radial.handle, toa or None, out.data_ptr(),
-                                     _stream(points.device, stream)))
+    _call(fn, points.device, lmax, n_atoms, centers.data_ptr(), offsets.data_ptr(), n_points, points.data_ptr(),
+          radial.handle, toa or None, out.data_ptr(), _stream(points.device, stream))
     return out
 
 
@@ -475,12 +477,9 @@ def sh_projectors_noalloc(lmax: int, centers: torch.Tensor, offsets: torch.Tenso
             raise ValueError("table_of_atom must be a contiguous int32 CUDA tensor of n_atoms entries")
         toa = table_of_atom.data_ptr()
     code = SH_F64 if dtype == torch.float64 else SH_F32
-    with torch.cuda.device(points.device):
-        check("sh_projectors_noalloc",
-              lib().sh_projectors_noalloc(lmax, code, n_atoms, centers.data_ptr(), offsets.data_ptr(), n_points,
-                                          points.data_ptr(), values.shape[0], values.shape[2], float(r_max),
-                                          values.data_ptr(), toa or None, out.data_ptr(),
-                                          _stream(points.device, stream)))
+    _call("sh_projectors_noalloc", points.device, lmax, code, n_atoms, centers.data_ptr(), offsets.data_ptr(),
+          n_points, points.data_ptr(), values.shape[0], values.shape[2], float(r_max), values.data_ptr(), toa or None,
+          out.data_ptr(), _stream(points.device, stream))
     return out
 
 

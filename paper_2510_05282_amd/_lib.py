@@ -104,6 +104,9 @@ def lib() -> ctypes.CDLL:
         getattr(L, fn).restype = i32
     L.sh_strerror.argtypes = [i32]
     L.sh_strerror.restype = ctypes.c_char_p
+    # of the HIP runtime that the library is linked to
+    L.hipStreamSynchronize.argtypes = [vp]
+    L.hipStreamSynchronize.restype = i32
     L.sh_last_hip_error.argtypes = []
     L.sh_last_hip_error.restype = i32
     _lib = L

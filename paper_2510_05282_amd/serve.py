@@ -106,8 +106,10 @@ class Server:
         """Returns a finished request's output memory to the server, which may give
         it to the next request's kernel at once: the work already queued on the
         current torch stream (a clone() of the result, say) is waited for first."""
-        if torch.cuda.is_available() and torch.cuda.is_initialized():
-            torch.cuda.current_stream().synchronize()
+        if torch.cuda.is_initialized():
+            # by its handle: a torch Stream object costs more than the wait of an idle stream
+            check("hipStreamSynchronize", 2 if lib().hipStreamSynchronize(
+                torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())) else 0)
         check("sh_server_release", lib().sh_server_release(self.handle, ticket))
 
     def drain(self, timeout_s: float = 600.0) -> None:
