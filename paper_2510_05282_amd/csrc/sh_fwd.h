@@ -42,8 +42,8 @@ struct StoreShape {
     size_t lds;  // LDS reserved (not used) per 256-thread workgroup
 };
 
-// LDS reservations out of a CU's 160 KiB: at most 3, 2 or 1 resident workgroups.
-constexpr size_t kCapLds3 = 40 * 1024, kCapLds2 = 54 * 1024, kCapLds1 = 84 * 1024;
+// LDS reservations out of a CU's 160 KiB: at most 4, 2 or 1 resident workgroups.
+constexpr size_t kCapLds4 = 40 * 1024, kCapLds2 = 54 * 1024, kCapLds1 = 84 * 1024;
 
 // Whether rows that start at p and lie row_bytes apart all start on a 128-byte line.
 inline bool on_lines(const void* p, int64_t row_bytes)
@@ -83,7 +83,7 @@ inline StoreShape store_shape(int64_t bytes, bool lines)
 {
     if (bytes < kWideBytes) return {false, 0};
     if (ROWS == 1) return {true, 0};
-    if (ROWS <= 4) return {false, sizeof(TIO) == 8 ? kCapLds3 : 0};
+    if (ROWS <= 4) return {false, sizeof(TIO) == 8 ? kCapLds4 : 0};
     if (ROWS <= 9) return {true, kCapLds2};
     if (lines && bytes < kCapBytes) return {true, 0};
     return {true, !lines || ROWS == 16 || (ROWS > 64 && sizeof(TIO) == 8) ? kCapLds1 : kCapLds2};

@@ -26,29 +26,40 @@ namespace shk {
 
 constexpr int kGradBlock = 256;
 constexpr int64_t kGradChunk = int64_t(1) << 28;
-// LDS reserved (not used) per workgroup of the backward kernel: at most 4 resident
-// workgroups (16 waves) per CU.  Measured on MI355X: 73% of 8 TB/s against 71.8%
-// uncapped (FP32: 74.1% against 71.0%).  Unlike the store-bound kernels, this
-// read-bound one runs best in plain workgroup order (XCD-contiguous order: 68.6%)
-// and with one point per lane: 2 adjacent points per lane (16-byte loads of G),
-// or 4 in FP32, measured 0-5% slower at lmax 3, 6 and 9 with every cap and order.
-constexpr size_t kGradCapLds = 40 * 1024;
+
+// How the reads of G are made and ordered (us, at the bytes of G; plain workgroup order and
+// at most 4 resident workgroups per CU unless said otherwise; one point per lane: two, or
+// four in FP32, are equal or up to 25% slower below 400 MB and within 5% above).
+//  kCached   below kReadCachedBytes, where G, which a caller has usually just written, is
+//            in the memory-side cache: loads that keep lines, XCD-contiguous order, no cap.
+//            FP64 lmax 4, 500001 points (100 MB) 18.0 against 22.7 streaming, lmax 9, 100001
+//            13.4 / 17.5; FP32 lmax 6, 400000 13.5 / 16.2
+//  kStream   larger: non-temporal loads.  Rows on 128-byte lines, FP64 lmax 6,
+//            2000000 147 against 158 with loads that keep lines and 167 as kCached; FP32
+//            145 / 156 / 167
+//  kShared   from kGradSharedBytes and lmax 3, rows off the lines: loads that keep lines,
+//            as neighbouring waves read parts of the same ones.  FP64 lmax 6, 4194301 331
+//            against 364 streaming, lmax 8, 2000001 250 / 260; FP32 lmax 8, 4000001 247 /
+//            270; but FP64 lmax 2, 8000001 153 / 149, lmax 5, 1000001 (288 MB) 61 / 58
+enum class GRead { kCached, kStream, kShared };
+constexpr int64_t kGradSharedBytes = int64_t(1) << 29;
 
 // TIO is the element type of xyz, G and the result; the normalisation and 1/r
 // run in FP64, the polynomials and the contraction in TIO.
-template <int LMAX, typename TIO>
+template <int LMAX, typename TIO, GRead READ>
 __global__ __launch_bounds__(kGradBlock) void grad_kernel(const TIO* __restrict__ xyz, const TIO* __restrict__ G,
                                                           TIO* __restrict__ gxyz, uint32_t n, int64_t ldg)
 {
-    const uint32_t i = blockIdx.x * kGradBlock + threadIdx.x;
+    const uint32_t b = READ == GRead::kCached ? xcd_tile(blockIdx.x, gridDim.x) : blockIdx.x;
+    const uint32_t i = b * kGradBlock + threadIdx.x;
     if (i >= n) return;
     const TIO* p = xyz + 3 * size_t(i);
     double xb, yb, zb, keep, rinv;
     normalize(double(p[0]), double(p[1]), double(p[2]), xb, yb, zb, keep, rinv);
     const uint32_t boff = i * uint32_t(sizeof(TIO));
     auto g_at = [&](int r) {
-        return __builtin_nontemporal_load(
-            reinterpret_cast<const TIO*>(reinterpret_cast<const char*>(G + int64_t(r) * ldg) + boff));
+        const TIO* g = reinterpret_cast<const TIO*>(reinterpret_cast<const char*>(G + int64_t(r) * ldg) + boff);
+        return READ == GRead::kStream ? __builtin_nontemporal_load(g) : *g;
     };
     (void)keep;  // the origin needs no mask here: rinv = 0 there, so the gradient is 0
     TIO vx, vy, vz;
@@ -61,18 +72,30 @@ __global__ __launch_bounds__(kGradBlock) void grad_kernel(const TIO* __restrict_
     o[2] = TIO(rinv * (double(vz) - zb * uv));
 }
 
-template <int LMAX, typename TIO>
-static hipError_t launch_grad_l(int64_t n, const TIO* xyz, const TIO* G, int64_t ldg, TIO* gxyz, hipStream_t s)
+template <int LMAX, typename TIO, GRead READ>
+static hipError_t launch_grad_one(int64_t n, const TIO* xyz, const TIO* G, int64_t ldg, TIO* gxyz, hipStream_t s)
 {
     for (int64_t c0 = 0; c0 < n; c0 += kGradChunk) {
         const int64_t nc = n - c0 < kGradChunk ? n - c0 : kGradChunk;
         const unsigned grid = unsigned((nc + kGradBlock - 1) / kGradBlock);
-        hipLaunchKernelGGL((grad_kernel<LMAX, TIO>), dim3(grid), dim3(kGradBlock), kGradCapLds, s, xyz + 3 * c0,
-                           G + c0, gxyz + 3 * c0, uint32_t(nc), ldg);
+        hipLaunchKernelGGL((grad_kernel<LMAX, TIO, READ>), dim3(grid), dim3(kGradBlock),
+                           READ == GRead::kCached ? 0 : kCapLds4, s, xyz + 3 * c0, G + c0, gxyz + 3 * c0, uint32_t(nc),
+                           ldg);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+template <int LMAX, typename TIO>
+static hipError_t launch_grad_l(int64_t n, const TIO* xyz, const TIO* G, int64_t ldg, TIO* gxyz, hipStream_t s)
+{
+    const int64_t bytes = n * nfun(LMAX) * int64_t(sizeof(TIO));
+    if (bytes < kReadCachedBytes) return launch_grad_one<LMAX, TIO, GRead::kCached>(n, xyz, G, ldg, gxyz, s);
+    if constexpr (LMAX >= 3)
+        if (bytes >= kGradSharedBytes && !on_lines(G, ldg * sizeof(TIO)))
+            return launch_grad_one<LMAX, TIO, GRead::kShared>(n, xyz, G, ldg, gxyz, s);
+    return launch_grad_one<LMAX, TIO, GRead::kStream>(n, xyz, G, ldg, gxyz, s);
 }
 
 template <typename TIO>

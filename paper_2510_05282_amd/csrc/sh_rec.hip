@@ -124,7 +124,7 @@ template hipError_t launch_rec<float>(int, int64_t, const float*, float*, int64_
 constexpr int64_t kGradRecNarrow = int64_t(1) << 16;
 template <typename TIO> constexpr int64_t kGradRecSplit = int64_t(1) << (sizeof(TIO) == 8 ? 18 : 20);
 
-template <typename TIO, int PPL, bool SPLIT, int UNROLL>
+template <typename TIO, int PPL, bool SPLIT, int UNROLL, bool NT>
 __global__ __launch_bounds__(kRecBlock, !SPLIT && sizeof(TIO) == 8 ? 4 : 1) void grad_rec_kernel(
     const TIO* __restrict__ xyz, const TIO* __restrict__ G, TIO* __restrict__ gxyz, uint32_t n, int64_t ldg, int lmax)
 {
@@ -149,8 +149,8 @@ __global__ __launch_bounds__(kRecBlock, !SPLIT && sizeof(TIO) == 8 ? 4 : 1) void
     }
     const uint32_t boff = i0 * uint32_t(sizeof(TIO));
     auto g_at = [&](int r) {
-        return V(__builtin_nontemporal_load(
-            reinterpret_cast<const U*>(reinterpret_cast<const char*>(G + int64_t(r) * ldg) + boff)));
+        const U* g = reinterpret_cast<const U*>(reinterpret_cast<const char*>(G + int64_t(r) * ldg) + boff);
+        return NT ? V(__builtin_nontemporal_load(g)) : V(*g);
     };
     V v[3];
     if constexpr (SPLIT) {
@@ -178,19 +178,20 @@ __global__ __launch_bounds__(kRecBlock, !SPLIT && sizeof(TIO) == 8 ? 4 : 1) void
     }
 }
 
-template <typename TIO, int PPL, bool SPLIT, int UNROLL>
+template <typename TIO, int PPL, bool SPLIT, int UNROLL, bool NT>
 static hipError_t launch_grad_rec_one(int lmax, int64_t n, const TIO* xyz, const TIO* G, int64_t ldg, TIO* gxyz,
                                       hipStream_t s)
 {
     constexpr int kLanes = SPLIT ? 64 : kRecBlock;
     const unsigned grid = unsigned(((n + PPL - 1) / PPL + kLanes - 1) / kLanes);
-    hipLaunchKernelGGL((grad_rec_kernel<TIO, PPL, SPLIT, UNROLL>), dim3(grid), dim3(kRecBlock), 0, s, xyz, G, gxyz,
+    hipLaunchKernelGGL((grad_rec_kernel<TIO, PPL, SPLIT, UNROLL, NT>), dim3(grid), dim3(kRecBlock), 0, s, xyz, G, gxyz,
                        uint32_t(n), ldg, lmax);
     return hipGetLastError();
 }
 
-template <typename TIO>
-hipError_t launch_grad_rec(int lmax, int64_t n, const TIO* xyz, const TIO* G, int64_t ldg, TIO* gxyz, hipStream_t s)
+template <typename TIO, bool NT>
+static hipError_t launch_grad_rec_nt(int lmax, int64_t n, const TIO* xyz, const TIO* G, int64_t ldg, TIO* gxyz,
+                                     hipStream_t s)
 {
     constexpr int kVec = 16 / sizeof(TIO);
     for (int64_t c0 = 0; c0 < n; c0 += kRecChunk) {
@@ -198,12 +199,23 @@ hipError_t launch_grad_rec(int lmax, int64_t n, const TIO* xyz, const TIO* G, in
         const TIO *x = xyz + 3 * c0, *g = G + c0;
         TIO* o = gxyz + 3 * c0;
         const hipError_t e =
-            n < kGradRecNarrow || nc < kVec ? launch_grad_rec_one<TIO, 1, true, 8>(lmax, nc, x, g, ldg, o, s)
-            : n < kGradRecSplit<TIO>        ? launch_grad_rec_one<TIO, 2, true, 2>(lmax, nc, x, g, ldg, o, s)
-                                            : launch_grad_rec_one<TIO, kVec, false, 2>(lmax, nc, x, g, ldg, o, s);
+            n < kGradRecNarrow || nc < kVec ? launch_grad_rec_one<TIO, 1, true, 8, NT>(lmax, nc, x, g, ldg, o, s)
+            : n < kGradRecSplit<TIO>        ? launch_grad_rec_one<TIO, 2, true, 2, NT>(lmax, nc, x, g, ldg, o, s)
+                                            : launch_grad_rec_one<TIO, kVec, false, 2, NT>(lmax, nc, x, g, ldg, o, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+// NT (non-temporal reads of G) from kReadCachedBytes on: lmax 16, 60001 points FP64 26.4 us
+// without, 29.5 with, FP32 100000 20.9 / 24.5; 200000 FP64 (462 MB) 88.5 / 78.0, FP32
+// 400000 89 / 79.
+template <typename TIO>
+hipError_t launch_grad_rec(int lmax, int64_t n, const TIO* xyz, const TIO* G, int64_t ldg, TIO* gxyz, hipStream_t s)
+{
+    return n * nfun(lmax) * int64_t(sizeof(TIO)) < kReadCachedBytes
+               ? launch_grad_rec_nt<TIO, false>(lmax, n, xyz, G, ldg, gxyz, s)
+               : launch_grad_rec_nt<TIO, true>(lmax, n, xyz, G, ldg, gxyz, s);
 }
 
 template hipError_t launch_grad_rec<double>(int, int64_t, const double*, const double*, int64_t, double*,
