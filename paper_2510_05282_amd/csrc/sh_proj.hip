@@ -103,7 +103,8 @@ __device__ __forceinline__ Affine block_before(Affine own, Affine* tot)
 // (a value of y that is not) or near overflow, one thread runs spline_solve, so that
 // infinities and NaN spread as there; `work` is where its pairs go when table is null.
 // Bound by latency: with one thread per channel 168 channels of 2000 knots took 1.48 ms
-// (0.74 us per knot, 168 lanes of the GPU busy); this takes 8 us.
+// (0.74 us per knot, 168 lanes of the GPU busy); this takes 9-11 us (13-14 before every load
+// of a tile and of the c_k was issued ahead of the first wait).
 __global__ __launch_bounds__(kSplineBlock) void spline_setup_kernel(const double* __restrict__ y,
                                                                     double2* __restrict__ table,
                                                                     float2* __restrict__ table_f32,
@@ -122,16 +123,29 @@ __global__ __launch_bounds__(kSplineBlock) void spline_setup_kernel(const double
     const int64_t at0 = c / ch * n_r * ch + c % ch;
     const int nt = (n_r + kSplineTile - 1) / kSplineTile;
     auto interior = [&](int k) { return k >= 1 && k <= n_r - 2; };
+    auto coefs = [&](int k0, double (&ck)[kSplinePer + 1]) {
+#pragma unroll
+        for (int i = 0; i <= kSplinePer; ++i) ck[i] = spline_c(k0 + i - 1 < 0 ? 0 : k0 + i - 1);
+    };
     double d[kSplinePer];
     double carry = 0.0;
     for (int t = 0; t < nt; ++t) {
         const int base = t * kSplineTile;
-        for (int j = tid; j < kSplineTile + 2; j += kSplineBlock) {  // slot j holds y[base - 1 + j]
-            const int k = base - 1 + j;
-            ys[spline_slot(j)] = k >= 0 && k < n_r ? yc[k] : 0.0;
+        // slot j holds y[base - 1 + j] (beyond the ends, where no interior knot looks, the
+        // end's value again); every load is issued before the first is waited for
+        double yv[kSplinePer + 1];
+#pragma unroll
+        for (int q = 0; q <= kSplinePer; ++q) {
+            const int k = base - 1 + tid + q * kSplineBlock;
+            yv[q] = yc[k < 0 ? 0 : (k < n_r ? k : n_r - 1)];
         }
-        __syncthreads();
+#pragma unroll
+        for (int q = 0; q <= kSplinePer; ++q)
+            if (q < kSplinePer || tid < 2) ys[spline_slot(tid + q * kSplineBlock)] = yv[q];
         const int k0 = base + tid * kSplinePer;
+        double ck[kSplinePer + 1];  // c_{k0 - 1} .. c_{k0 + kSplinePer - 1}, asked for together
+        coefs(k0, ck);
+        __syncthreads();
         bool bad = false;
         Affine own{1.0, 0.0};
 #pragma unroll
@@ -140,9 +154,8 @@ __global__ __launch_bounds__(kSplineBlock) void spline_setup_kernel(const double
             const double rhs = six_over_h2 * (ys[spline_slot(j + 2)] - 2.0 * ys[spline_slot(j + 1)] + ys[spline_slot(j)]);
             d[i] = rhs;
             if (interior(k0 + i)) {
-                const double ck = spline_c(k0 + i);
-                own.b = (rhs - own.b) * ck;
-                own.a = -own.a * ck;
+                own.b = (rhs - own.b) * ck[i + 1];
+                own.a = -own.a * ck[i + 1];
                 bad = bad || !(fabs(rhs) < 0x1p+1000);
             } else {
                 own = Affine{0.0, 0.0};
@@ -165,8 +178,8 @@ __global__ __launch_bounds__(kSplineBlock) void spline_setup_kernel(const double
         for (int i = 0; i < kSplinePer; ++i) {
             if (interior(k0 + i)) {
                 // (rhs - v) / (4 - c_{k-1}) through the reciprocal c_k and one correction
-                const double ck = spline_c(k0 + i), x = d[i] - v, den = 4.0 - spline_c(k0 + i - 1), q = x * ck;
-                v = __builtin_fma(__builtin_fma(-q, den, x), ck, q);
+                const double x = d[i] - v, den = 4.0 - ck[i], q = x * ck[i + 1];
+                v = __builtin_fma(__builtin_fma(-q, den, x), ck[i + 1], q);
             } else {
                 v = 0.0;
             }
@@ -180,14 +193,15 @@ __global__ __launch_bounds__(kSplineBlock) void spline_setup_kernel(const double
     carry = 0.0;
     for (int t = nt - 1; t >= 0; --t) {
         const int base = t * kSplineTile, k0 = base + tid * kSplinePer;
+        double ck[kSplinePer + 1];
+        coefs(k0, ck);
         Affine own{1.0, 0.0};
 #pragma unroll
         for (int i = kSplinePer - 1; i >= 0; --i) {
             if (nt > 1) d[i] = k0 + i < n_r ? dc[k0 + i] : 0.0;
             if (interior(k0 + i)) {
-                const double ck = spline_c(k0 + i);
-                own.b = d[i] - ck * own.b;
-                own.a = -ck * own.a;
+                own.b = d[i] - ck[i + 1] * own.b;
+                own.a = -ck[i + 1] * own.a;
             } else {
                 own = Affine{0.0, 0.0};
             }
@@ -196,7 +210,7 @@ __global__ __launch_bounds__(kSplineBlock) void spline_setup_kernel(const double
         double v = m.a * carry + m.b;
 #pragma unroll
         for (int i = kSplinePer - 1; i >= 0; --i) {
-            v = interior(k0 + i) ? d[i] - spline_c(k0 + i) * v : 0.0;
+            v = interior(k0 + i) ? d[i] - ck[i + 1] * v : 0.0;
             ms[spline_slot(tid * kSplinePer + i)] = v;
         }
         if (tid == 0) edge = v;
@@ -581,11 +595,11 @@ hipError_t launch_spline_setup(const double* y, double2* table, float2* table_f3
 {
     // a dispatch counts its work-items in 32 bits
     constexpr int64_t kChunk = int64_t(1) << 22;
-    // A workgroup per channel costs 8.5 us per 1000 channels whatever their length up to
+    // A workgroup per channel costs 7 us per 1000 channels whatever their length up to
     // kSplineTile, a thread per channel about 0.75 us per knot until the lanes fill the GPU.
     // Measured, thread against workgroup per channel, with a one-tile build after it:
-    // 260000 x 8 knots 50 / 1874 us, 10000 x 64 55 / 90, 16000 x 128 104 / 148, 1000 x 16
-    // 18 / 17, 8000 x 256 202 / 84, 168 x 300 190 / 17, 168 x 2000 1390 / 18.
+    // 260000 x 8 knots 50 / 1568 us, 10000 x 64 56 / 72, 16000 x 128 106 / 115, 1000 x 16
+    // 18 / 16, 8000 x 256 201 / 67, 168 x 300 191 / 12, 168 x 2000 1395 / 16.
     const bool serial = n_ch > int64_t(96) * n_r;
     for (int64_t c0 = 0; c0 < n_ch; c0 += kChunk) {
         const int64_t nc = n_ch - c0 < kChunk ? n_ch - c0 : kChunk;
