@@ -160,14 +160,16 @@ static hipError_t launch_mixed(int64_t tiles, const ServeInline& in, const Serve
     return hipGetLastError();
 }
 
-// Lane width and LDS reservation (resident workgroups per CU) of the vector-lane serving
-// launches.
+// Lane width and LDS reservation of the vector-lane serving launches: one resident
+// workgroup per CU from lmax 5, two below (see proj_cap_lds; rows of a request start
+// anywhere, as an atom's do).  Closed loop of 2500 requests, two processes each: from lmax
+// 5 111.2-111.5k req/s, from 6 110.4-110.6k, from 7 109.7-110.1k, from 8 107.8-108.3k (FP64
+// from 8, FP32 from 9: 107.2-107.8k); Poisson p50 and p99 at 23k, 54k and 75k req/s equal.
 template <typename TIO, int LMAX>
 constexpr int kServePpl = sizeof(TIO) == 4 ? 4 : (LMAX == 1 || LMAX == 2 ? 4 : 2);
 template <typename TIO, int LMAX>
-constexpr size_t kServeCapLds = (LMAX == 9 || (sizeof(TIO) == 8 && LMAX == 8))
-                                    ? kCapLds1
-                                    : ((sizeof(TIO) == 4 ? LMAX <= 1 : LMAX == 0) ? 0 : kCapLds2);
+constexpr size_t kServeCapLds =
+    LMAX >= 5 ? kCapLds1 : ((sizeof(TIO) == 4 ? LMAX <= 1 : LMAX == 0) ? 0 : kCapLds2);
 
 template <int LMAX, typename TIO>
 static void launch_group_l(int ppl, int64_t tiles, const ServeInline& in, const ServeDesc* descs,
