@@ -75,7 +75,8 @@ inline bool on_lines(const void* p, int64_t row_bytes)
 //  the same on lines,  below 2^29 bytes: FP64 lmax 9, 2^19 2/0 77.2, 2/84 80.4; FP32 lmax
 //                      5, 2^21 4/0 61.3, 4/84 63.6; complex FP64 lmax 6, 250000 1/0 38.0,
 //                      1/54 39.3.  Above: FP64 lmax 3, 2^25 2/84 875, 2/54 910, lmax 4 1386,
-//                      1375, lmax 9 at 2^26 68.4% of 8 TB/s against 67.8%; FP32 equal
+//                      1375, lmax 9 at 2^26 68.4% of 8 TB/s against 67.8%; Jacobian lmax 8
+//                      (324 rows), 703552 345 / 342; FP32 equal
 constexpr int64_t kWideBytes = int64_t(1) << 27, kCapBytes = int64_t(1) << 29;
 
 template <int ROWS, typename TIO>
@@ -86,7 +87,7 @@ inline StoreShape store_shape(int64_t bytes, bool lines)
     if (ROWS <= 4) return {false, sizeof(TIO) == 8 ? kCapLds4 : 0};
     if (ROWS <= 9) return {true, kCapLds2};
     if (lines && bytes < kCapBytes) return {true, 0};
-    return {true, !lines || ROWS == 16 || (ROWS > 64 && sizeof(TIO) == 8) ? kCapLds1 : kCapLds2};
+    return {true, !lines || ROWS == 16 || (ROWS > 64 && ROWS <= 100 && sizeof(TIO) == 8) ? kCapLds1 : kCapLds2};
 }
 
 // First point of lane `t` of a launch whose lanes take PPL adjacent points of n >= PPL
