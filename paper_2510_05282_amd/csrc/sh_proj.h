@@ -207,12 +207,13 @@ __device__ __forceinline__ void proj_points(const double (&px)[PPL], const doubl
 template <typename TIO> constexpr int kProjPpl = 16 / int(sizeof(TIO));
 
 // Builds of at least this many points, or bytes written, take several points per lane
-// (proj_launch in sh_proj.hip): below, a launch lasts its workgroups' chain of work, which
-// wider lanes lengthen.  us, one point against several: FP64 lmax 6, 24 x 4189 points (41
-// MB) 10.7 / 14.6; lmax 1, 64 x 14137 (50 MB) 13.1 / 15.5; FP32 lmax 3 (68 MB) 14.8 / 17.8;
-// FP64 lmax 4, 64 x 8000 (114 MB) 32.5 / 30.6; lmax 3, 64 x 14137 (136 MB) 41.8 / 39.4;
-// lmax 9 (738 MB) 201 / 171.
-constexpr int64_t kProjVecPoints = int64_t(1) << 20, kProjVecBytes = int64_t(3) << 25;
+// (launch_proj_l in sh_proj.hip): below, a launch lasts its workgroups' chain of work, which
+// wider lanes lengthen, and what it writes stays in the memory-side cache.  us, one point
+// against several: FP64 lmax 6, 24 x 4189 points (41 MB) 10.7 / 14.6; lmax 1, 64 x 14137 (50
+// MB) 13.0 / 18.0; FP32 lmax 3 (68 MB) 14.6 / 22.5; FP64 lmax 3, 904673 points (116 MB) into
+// one output 24.4 / 30.7, three outputs in turn 27.0 / 31.8, inputs and outputs out of the
+// caches 42.2 / 38.5; lmax 4 (181 MB) 32 / 38, 41 / 43; lmax 6 (355 MB) 118 / 98, 117 / 97.
+constexpr int64_t kProjVecPoints = int64_t(1) << 20, kProjVecBytes = int64_t(1) << 28;
 
 // LDS reserved (not used) by proj_kernel with several points per lane: at most 2 resident
 // workgroups per CU, or 1.  Fewer waves at once keep each row's concurrent writes in a
@@ -224,15 +225,18 @@ constexpr int64_t kProjVecPoints = int64_t(1) << 20, kProjVecBytes = int64_t(3) 
 // 254 / 243, lmax 6 313 / 297 / 272, lmax 7 340 / 321 / 290, lmax 9 384 / 388 / 348; FP32
 // lmax 3 127 / 114 / -, lmax 4 190 / 154 / -, lmax 5 238 / 217 / 212, lmax 6 254 / 244 /
 // 228, lmax 8 266 / 254 / 236, lmax 9 329 / 314 / 285.  200 atoms, 2 / 1: FP64 lmax 5 268 /
-// 287, lmax 6 280 / 293, lmax 7 255 / 237; FP32 lmax 6 201 / 218, lmax 8 182 / 175.
+// 287, lmax 6 280 / 293, lmax 7 255 / 237; FP32 lmax 6 201 / 218, lmax 8 182 / 175.  The
+// offsets are on the device; a total that deals every atom the same whole number of 128-byte
+// lines is taken for rows on lines: 64 x 150000, FP64 lmax 5 601 / 616, lmax 6 791 / 812.
 template <typename TIO, int LMAX>
-inline size_t proj_cap_lds(int n_atoms)
+inline size_t proj_cap_lds(int n_atoms, int64_t n_points)
 {
     constexpr bool f64 = sizeof(TIO) == 8;
     if (f64 ? LMAX == 0 : LMAX <= 1) return 0;
     if (LMAX <= 4) return kCapLds2;
     if (LMAX >= (f64 ? 7 : 8)) return kCapLds1;
-    return n_atoms > 64 ? kCapLds2 : kCapLds1;
+    const bool lines = n_atoms > 0 && n_points % (int64_t(n_atoms) * (128 / int64_t(sizeof(TIO)))) == 0;
+    return n_atoms > 64 || (f64 && lines) ? kCapLds2 : kCapLds1;
 }
 
 // Wave-wide search over n sorted keys: the last k in [0, n) with keys[k] <= x,

@@ -499,8 +499,9 @@ static int64_t proj_lds_bytes(int n_r)
 }
 
 // Whether a large build takes proj_lds_kernel (both sides measured, see there): the table
-// has the build's channels (a handle keeps such copies) and fits, an atom has enough points on average for its load, and at the lmax where the
-// launch without LDS is as fast over few atoms, the atoms are many or the points.
+// has the build's channels (a handle keeps such copies) and fits, an atom has enough
+// points on average for its load, and where the launch without LDS is as fast over few
+// atoms, the atoms or the points are many.
 template <typename TIO, int LMAX>
 static bool use_proj_lds(const ProjArgs<TIO>& A)
 {
@@ -541,7 +542,7 @@ static hipError_t launch_proj_l(const ProjArgs<TIO>& A, hipStream_t s)
     if (A.n_points < kProjVecPoints && A.n_points * nfun(LMAX) * int64_t(sizeof(TIO)) < kProjVecBytes)
         return launch_proj_p<LMAX, TIO, 1>(A, g, 0, s);
     if (use_proj_lds<TIO, LMAX>(A)) return launch_proj_lds<LMAX, TIO>(A, g, s);
-    return launch_proj_p<LMAX, TIO, kProjPpl<TIO>>(A, g, proj_cap_lds<TIO, LMAX>(A.n_atoms), s);
+    return launch_proj_p<LMAX, TIO, kProjPpl<TIO>>(A, g, proj_cap_lds<TIO, LMAX>(A.n_atoms, A.n_points), s);
 }
 
 template <typename TIO>
