@@ -258,9 +258,7 @@ __global__ __launch_bounds__(64) void spline_serial_kernel(const double* __restr
 // point loads and the arithmetic.  Otherwise, and for lanes past atom aw + 1, the
 // wave's atom comes from a wave-wide search and a lane's from a binary search, and
 // the atom's data is loaded after it.  Measured on the 64-atom lmax 3 build (one
-// point per lane): 29.6-29.8 us -> 27.6-28.0 us.  The launches with several points per
-// lane keep the search: there the preload alone cost as much as the shorter chain saved
-// (-6% to +5% across lmax and dtype on 64 x 150k-point builds).
+// point per lane): 29.6-29.8 us -> 27.6-28.0 us.  Which launches take it: kProjSmall.
 struct AtomRef {
     int64_t o0, o1;  // its point range
     double c[3];
@@ -369,7 +367,7 @@ __global__ __launch_bounds__(256) void proj_kernel(const TIO* __restrict__ cente
 // or two.  Offsets that are inconsistent around a tile send the rest of it through the
 // points one by one, as proj_kernel.  The same arithmetic, so the same bits.
 // us against the best launch without LDS: 64 x 150k points FP64 lmax 1 116-122 / 141, FP32
-// lmax 2 109-112 / 124, lmax 3 161 / 160, lmax 4 164 / 155, FP64 lmax 2 (64 x 100k) 143 /
+// lmax 2 109-112 / 124, lmax 3 160 / 157, lmax 4 164 / 155, FP64 lmax 2 (64 x 100k) 143 /
 // 147, lmax 3 345 / 304; 200 x 20k FP32 lmax 3 76 / 88, lmax 4 110 / 118; 1024 x 9400 FP32
 // lmax 0 43 / 59, lmax 2 120 / 167, lmax 3 179 / 224, FP64 lmax 0 74 / 107, lmax 1 135 /
 // 192, lmax 3 361 / 392; 512 x 4000 FP32 lmax 2 34 / 46, FP64 lmax 1 37 / 45.
@@ -465,14 +463,21 @@ __global__ __launch_bounds__(BT) void proj_lds_kernel(const TIO* __restrict__ ce
 // dispatch (a multiple of every lane width, so only the last launch has a tail).
 constexpr int64_t kProjChunk = int64_t(1) << 28;
 
+// The atoms of a launch over at most 64 are loaded into the lanes together with the points
+// and found by a ballot, instead of by a search over the offsets first (a chain of dependent
+// loads).  us with and without, 2 workgroups per CU, several points per lane: FP64 lmax 3, 64 x
+// 14137 points 38.3 / 39.5, 64 x 150000 309 / 313; FP32 lmax 3 157 / 162, lmax 4, 64 x 50000
+// 86.9 / 90.9; from lmax 5 on equal, so only the search there.
+template <int P, int LMAX> constexpr bool kProjSmall = P == 1 || LMAX <= 4;
+
 template <int LMAX, typename TIO, int P>
 static hipError_t launch_proj_p(const ProjArgs<TIO>& A, const SplineGrid& g, size_t lds, hipStream_t s)
 {
     for (int64_t j0 = 0; j0 < A.n_points; j0 += kProjChunk) {
         const int64_t nc = A.n_points - j0 < kProjChunk ? A.n_points - j0 : kProjChunk;
         const dim3 grid = dim3(unsigned((nc + 256 * P - 1) / (256 * P))), block = dim3(256);
-        if (P == 1 && A.n_atoms <= 64)
-            hipLaunchKernelGGL((proj_kernel<LMAX, TIO, P, P == 1>), grid, block, lds, s, A.centers, A.offsets,
+        if (kProjSmall<P, LMAX> && A.n_atoms <= 64)
+            hipLaunchKernelGGL((proj_kernel<LMAX, TIO, P, kProjSmall<P, LMAX>>), grid, block, lds, s, A.centers, A.offsets,
                                A.n_atoms, A.points, A.n_points, A.table, A.tab_ch, A.n_tables, A.table_of_atom, g,
                                A.out, j0);
         else
@@ -514,7 +519,7 @@ static bool use_proj_lds(const ProjArgs<TIO>& A)
         if (LMAX == 2) return A.n_atoms > 64 || A.n_points >= int64_t(1) << 22;
         return LMAX == 1 || A.n_atoms > 128;
     }
-    return LMAX <= 3 || A.n_atoms > 64;
+    return LMAX <= 2 || A.n_atoms > 64;
 }
 
 template <int LMAX, typename TIO>
