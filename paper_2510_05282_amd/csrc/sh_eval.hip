@@ -37,6 +37,14 @@ struct Inputs {
         if constexpr (MODE == In::kAngles) return {a + c0, b + c0};
         else return {a + 3 * c0, b};
     }
+    // whether the angles of n points share memory with out[0 .. len)
+    bool shares(const TIO* out, int64_t n, int64_t len) const
+    {
+        auto meets = [&](const TIO* p) {
+            return uintptr_t(p) < uintptr_t(out + len) && uintptr_t(out) < uintptr_t(p + n);
+        };
+        return MODE == In::kAngles && (meets(a) || meets(b));
+    }
 };
 
 template <int LMAX, typename TIO, int PPL, In MODE>
@@ -61,11 +69,15 @@ static hipError_t launch_fwd_l(int64_t n, Inputs<MODE, TIO> in, TIO* out, int64_
     // 1500000 43.4 / 48.0 / 45.6; FP32 lmax 1, 9000001 64 / 86 / 94; lmax 6, 1000001 43.4 /
     // 45.9 / 52.4)
     if (kBusy && n * nfun(LMAX) * int64_t(sizeof(TIO)) >= kWideBytes) f = {LMAX != 2 || sizeof(TIO) == 4, 0};
+    // angles may be rows of out, as every point's are read before its values are written:
+    // then no lane reads a neighbour's, and a remainder takes one point per lane
+    const bool in_place = in.shares(out, n, (nfun(LMAX) - 1) * ld + n);
     for (int64_t c0 = 0; c0 < n; c0 += kChunk) {
         const int64_t nc = n - c0 < kChunk ? n - c0 : kChunk;
-        const hipError_t e = f.wide && nc >= kVec
-                                 ? launch_one<LMAX, TIO, kVec, MODE>(in.at(c0), out + c0, nc, ld, s, f.lds)
-                                 : launch_one<LMAX, TIO, 1, MODE>(in.at(c0), out + c0, nc, ld, s, f.lds);
+        const int64_t nw = !f.wide || nc < kVec ? 0 : in_place ? nc / kVec * kVec : nc;
+        hipError_t e = nw ? launch_one<LMAX, TIO, kVec, MODE>(in.at(c0), out + c0, nw, ld, s, f.lds) : hipSuccess;
+        if (e == hipSuccess && nw < nc)
+            e = launch_one<LMAX, TIO, 1, MODE>(in.at(c0 + nw), out + c0 + nw, nc - nw, ld, s, f.lds);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -166,15 +166,27 @@ __global__ __launch_bounds__(kRecBlock, !SPLIT && sizeof(TIO) == 8 ? 4 : 1) void
     } else {
         grad_unit_rec<V, UNROLL>(x, y, z, lmax, g_at, v[0], v[1], v[2]);
     }
+    // gxyz may be xyz: a last lane that read its neighbour's points too, which may be
+    // gradients by then, stores only its own
     TIO* o = gxyz + 3 * size_t(i0);
+    const int first = PPL > 1 ? int(t * PPL - i0) : 0;
+    TIO r[3 * PPL];
 #pragma unroll
     for (int q = 0; q < PPL; ++q) {
         const double gx = double(lane<V, PPL>(v[0], q)), gy = double(lane<V, PPL>(v[1], q)),
                      gz = double(lane<V, PPL>(v[2], q));
         const double uv = xb[q] * gx + yb[q] * gy + zb[q] * gz;
-        o[3 * q + 0] = TIO(rinv[q] * (gx - xb[q] * uv));
-        o[3 * q + 1] = TIO(rinv[q] * (gy - yb[q] * uv));
-        o[3 * q + 2] = TIO(rinv[q] * (gz - zb[q] * uv));
+        r[3 * q + 0] = TIO(rinv[q] * (gx - xb[q] * uv));
+        r[3 * q + 1] = TIO(rinv[q] * (gy - yb[q] * uv));
+        r[3 * q + 2] = TIO(rinv[q] * (gz - zb[q] * uv));
+    }
+    if (first == 0) {
+#pragma unroll
+        for (int k = 0; k < 3 * PPL; ++k) o[k] = r[k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < 3 * PPL; ++k)
+            if (k >= 3 * first) o[k] = r[k];
     }
 }
 
