@@ -107,6 +107,8 @@ def lib() -> ctypes.CDLL:
     # of the HIP runtime that the library is linked to
     L.hipStreamSynchronize.argtypes = [vp]
     L.hipStreamSynchronize.restype = i32
+    L.hipGetLastError.argtypes = []
+    L.hipGetLastError.restype = i32
     L.sh_last_hip_error.argtypes = []
     L.sh_last_hip_error.restype = i32
     _lib = L

@@ -6,7 +6,7 @@ import ctypes
 import numpy as np
 import torch
 
-from ._lib import ServerStats, check, lib
+from ._lib import ServerStats, ShError, check, lib
 
 SH_F64, SH_F32 = 0, 1
 SH_REQ_AUTORELEASE = 1
@@ -108,8 +108,10 @@ class Server:
         current torch stream (a clone() of the result, say) is waited for first."""
         if torch.cuda.is_initialized():
             # by its handle: a torch Stream object costs more than the wait of an idle stream
-            check("hipStreamSynchronize", 2 if lib().hipStreamSynchronize(
-                torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())) else 0)
+            rc = lib().hipStreamSynchronize(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+            if rc != 0:
+                lib().hipGetLastError()  # reported here, so not by the next call's check as well
+                raise ShError("hipStreamSynchronize", 2, rc)
         check("sh_server_release", lib().sh_server_release(self.handle, ticket))
 
     def drain(self, timeout_s: float = 600.0) -> None:
