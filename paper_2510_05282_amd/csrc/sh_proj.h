@@ -239,25 +239,44 @@ inline size_t proj_cap_lds(int n_atoms, int64_t n_points)
     return n_atoms > 64 || (f64 && lines) ? kCapLds2 : kCapLds1;
 }
 
-// Wave-wide search over n sorted keys: the last k in [0, n) with keys[k] <= x,
-// or -1 if there is none.  Every lane must be active and pass the same x; each
-// round the 64 lanes probe 64 evenly spaced keys and a ballot keeps the bracket,
-// so n keys take ceil(log64 n) dependent loads.  Keys that are not sorted still
-// give some k in [0, n) (callers check what they use).
-__device__ __forceinline__ int wave_search(const int64_t* __restrict__ keys, int n, int64_t x)
+// Wave-wide searches, N at once over the same n sorted keys: at[i] = the last k in [0, n)
+// with key(k) <= x[i], or -1 if there is none.  Every lane must be active and pass the same
+// x; each round the 64 lanes probe 64 evenly spaced keys and a ballot keeps the bracket, so
+// n keys take ceil(log64 n) dependent loads.  Keys that are not sorted still give some k
+// in [0, n) or -1 (callers check what they use).
+template <int N, typename Key>
+__device__ __forceinline__ void wave_searches(int n, Key&& key, const int64_t (&x)[N], int (&at)[N])
 {
     const int lane = threadIdx.x & 63;
-    int lo = 0, hi = n;  // the answer lies in [lo, hi)
-    while (hi - lo > 1) {
-        const int step = (hi - lo + 63) / 64;
-        const int k = lo + lane * step;
-        const bool pred = k < hi && keys[k] <= x;
-        const int c = __popcll(__ballot(pred));  // lanes 0 .. c-1 probe keys <= x
-        if (c == 0) return -1;
-        lo += (c - 1) * step;
-        hi = min(lo + step, hi);
+    int lo[N], hi[N];  // the answers lie in [lo, hi)
+    bool none[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) lo[i] = 0, hi[i] = n, none[i] = false;
+    for (int width = n, first = 1; width > 1 || first; first = 0) {
+        width = 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int step = (hi[i] - lo[i] + 63) / 64;
+            const int k = lo[i] + lane * step;
+            const bool pred = k < hi[i] && key(k) <= x[i];
+            const int c = __popcll(__ballot(pred));  // lanes 0 .. c-1 probe keys <= x
+            none[i] = none[i] || c == 0;
+            lo[i] += c > 0 ? (c - 1) * step : 0;
+            hi[i] = c > 0 ? min(lo[i] + step, hi[i]) : lo[i];
+            width = max(width, hi[i] - lo[i]);
+        }
     }
-    return keys[lo] <= x ? lo : -1;
+#pragma unroll
+    for (int i = 0; i < N; ++i) at[i] = none[i] ? -1 : lo[i];
+}
+
+// One of them over an array.
+__device__ __forceinline__ int wave_search(const int64_t* __restrict__ keys, int n, int64_t x)
+{
+    const int64_t xs[1] = {x};
+    int at[1];
+    wave_searches<1>(n, [&](int k) { return keys[k]; }, xs, at);
+    return at[0];
 }
 
 // The value v holds in lane k of the wave; k must be the same in every lane (one

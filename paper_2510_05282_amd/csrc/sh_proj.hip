@@ -356,16 +356,60 @@ __global__ __launch_bounds__(256) void proj_kernel(const TIO* __restrict__ cente
     }
 }
 
+// Points w0 .. w0 + 63 of a wave, those below `end`, one per lane and of any atoms, from
+// tables of LMAX + 1 channels in memory.  The 64 offsets after the wave's first atom are held
+// in the lanes, where each lane finds its atom; only points beyond them search on.
+template <int LMAX, typename TIO>
+__device__ __forceinline__ void proj_wave(const TIO* __restrict__ centers, const int64_t* __restrict__ offsets,
+                                          int n_atoms, const TIO* __restrict__ points, int64_t n_points,
+                                          const knot_t<TIO>* __restrict__ table, int n_tables,
+                                          const int32_t* __restrict__ table_of_atom, const SplineGrid& g,
+                                          TIO* __restrict__ out, int64_t w0, int64_t end)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t j = w0 + lane;
+    const TIO* p = points + 3 * (j < end ? j : w0);
+    const double px = double(p[0]), py = double(p[1]), pz = double(p[2]);
+    const int aw = max(wave_search(offsets, n_atoms, w0), 0);
+    const int64_t after = offsets[min(aw + 1 + lane, n_atoms)];
+    int k = 0;  // how many of them are <= j (63 at most)
+#pragma unroll
+    for (int s = 32; s > 0; s /= 2)
+        if (__shfl(after, k + s - 1) <= j) k += s;
+    if (j >= end) return;
+    int a = min(aw + k, n_atoms - 1);
+    int64_t o0 = offsets[a], o1 = offsets[a + 1];
+    if (!(o0 <= j && j < o1)) {
+        a = lane_search(offsets, n_atoms, j);
+        o0 = offsets[a];
+        o1 = offsets[a + 1];
+    }
+    if (!(o0 >= 0 && o0 <= j && j < o1 && o1 <= n_points)) return;
+    const double c[3] = {double(centers[3 * a]), double(centers[3 * a + 1]), double(centers[3 * a + 2])};
+    int t = table_of_atom ? table_of_atom[a] : a;
+    t = t < 0 ? 0 : (t >= n_tables ? n_tables - 1 : t);
+    proj_point<LMAX, TIO>(px, py, pz, c, table + int64_t(t) * g.n_r * (LMAX + 1), LMAX + 1, g,
+                          out + nfun(LMAX) * o0 + (j - o0), o1 - o0);
+}
+
 // Persistent build for small lmax: a workgroup keeps the spline table of the atom it works
 // on in LDS (of LMAX + 1 channels) and walks tiles of BT * PPL points.  A lookup
 // scatters its lanes over as many cache lines, one tag check each: at lmax 3 in FP32 two
 // thirds of the L1's cycles went there, and where the tables of many atoms outgrow the L2
 // it waited for them as well.  Workgroups form groups of `group` (of the logical order, so
-// in one XCD), each with group_points consecutive points, whose tiles its workgroups take
-// in turn: with group = 32 an XCD's CUs write side by side, which the HBM write path
-// rewards, and each loads every table of the range; with group = 1 a workgroup loads one
-// or two.  Offsets that are inconsistent around a tile send the rest of it through the
-// points one by one, as proj_kernel.  The same arithmetic, so the same bits.
+// in one XCD), each with consecutive points, whose tiles its workgroups take in turn: with
+// group = 32 an XCD's CUs write side by side, which the HBM write path rewards, and each
+// loads every table of the range; with group = 1 a workgroup loads one or two.
+// A table costs as much as load_cost points, and so does an atom that has few of them: the
+// points are dealt out by that cost (an atom's place in it is its offset plus its number of
+// load costs, so a search finds a share's ends), and a run of fewer points than load_cost
+// whose table is not the one held goes through memory, one point per lane, with what follows
+// it, as do offsets that are inconsistent.  One atom of 3M points among 1000 of 10, in us
+// with a table load for each atom and equal points, so, and without LDS: FP32 lmax 0 1329 / 15 /
+// 22, lmax 2 2140 / 42 / 51, lmax 4 2821 / 113 / 89, FP64 lmax 1 1809 / 45 / 53, lmax 3 1492 /
+// 126 / 103; four of 800000 among 300 of 300 FP32 lmax 0 64 / 26 / 17, lmax 2 189 / 47 / 45, lmax
+// 4 176 / 120 / 85, FP64 lmax 1 167 / 46 / 55, lmax 3 176 / 136 / 110.  The same arithmetic, so
+// the same bits.
 // us against the best launch without LDS: 64 x 150k points FP64 lmax 1 116-122 / 141, FP32
 // lmax 2 109-112 / 124, lmax 3 160 / 157, lmax 4 164 / 155, FP64 lmax 2 (64 x 100k) 143 /
 // 147, lmax 3 345 / 304; 200 x 20k FP32 lmax 3 76 / 88, lmax 4 110 / 118; 1024 x 9400 FP32
@@ -377,49 +421,66 @@ __global__ __launch_bounds__(BT) void proj_lds_kernel(const TIO* __restrict__ ce
                                                       const TIO* __restrict__ points, int64_t n_points,
                                                       const knot_t<TIO>* __restrict__ table,
                                                       int n_tables, const int32_t* __restrict__ table_of_atom,
-                                                      SplineGrid g, TIO* __restrict__ out, int64_t group_points,
-                                                      int group)
+                                                      SplineGrid g, TIO* __restrict__ out, int64_t group_cost,
+                                                      int group, int load_cost)
 {
     using KN = knot_t<TIO>;
     constexpr int F = nfun(LMAX), CH = LMAX + 1;
     extern __shared__ __align__(16) unsigned char lds[];
     KN* tab = reinterpret_cast<KN*>(lds);
     const uint32_t w = xcd_tile(blockIdx.x, gridDim.x);
-    const int64_t g0 = int64_t(w / group) * group_points;
-    const int64_t g1 = g0 + group_points < n_points ? g0 + group_points : n_points;
-    int64_t o0 = 0, o1 = -1;  // point range of the current atom (none yet)
-    int a = -1, t = -1;       // the atom, and the table held in LDS
+    // the group's share: load_cost units before each atom's points, one for each of them
+    const int64_t gi = w / group, cost = n_points + int64_t(n_atoms) * load_cost;
+    const int64_t x[2] = {gi * group_cost, (gi + 1) * group_cost};
+    int at[2];
+    wave_searches<2>(n_atoms, [&](int k) { return offsets[k] + int64_t(k) * load_cost; }, x, at);
+    int64_t from[2], till[2], begin[2];  // the atom that each end of the share lies in, and where
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int b = max(at[i], 0);
+        from[i] = offsets[b];
+        till[i] = offsets[b + 1];
+        const int64_t in = x[i] - (from[i] + (int64_t(b) + 1) * load_cost);
+        const int64_t p = in <= 0 ? from[i] : (in < till[i] - from[i] ? from[i] + in / 64 * 64 : till[i]);
+        begin[i] = x[i] >= cost ? n_points : (p < 0 || x[i] == 0 ? 0 : (p < n_points ? p : n_points));
+    }
+    const int64_t g0 = begin[0], g1 = begin[1];
+    int a = at[0];                          // the atom looked at last
+    int64_t o0 = from[0], o1 = till[0];     // its points
+    bool here = false;                      // whether it is the current one
+    int t = -1;                             // the table held in LDS
     double c[3] = {};
     for (int64_t p0 = g0 + int64_t(w % group) * (BT * PPL); p0 < g1; p0 += int64_t(group) * (BT * PPL)) {
         const int64_t p1 = p0 + BT * PPL < g1 ? p0 + BT * PPL : g1;
         int64_t pos = p0;
         while (pos < p1) {
-            if (!(o0 <= pos && pos < o1)) {
-                a = wave_search(offsets, n_atoms, pos);
-                o0 = a >= 0 ? offsets[a] : 0;
-                o1 = a >= 0 ? offsets[a + 1] : -1;
-                if (o0 < 0 || !(o0 <= pos && pos < o1) || o1 > n_points) {
-                    // inconsistent here: this tile's points one by one
-                    o1 = -1;
-                    for (int64_t j = pos + threadIdx.x; j < p1; j += BT) {
-                        const int b = lane_search(offsets, n_atoms, j);
-                        const int64_t b0 = offsets[b], b1 = offsets[b + 1];
-                        if (!(b0 >= 0 && b0 <= j && j < b1 && b1 <= n_points)) continue;
-                        const double cb[3] = {double(centers[3 * b]), double(centers[3 * b + 1]),
-                                              double(centers[3 * b + 2])};
-                        int tb = table_of_atom ? table_of_atom[b] : b;
-                        tb = tb < 0 ? 0 : (tb >= n_tables ? n_tables - 1 : tb);
-                        proj_point<LMAX, TIO>(double(points[3 * j]), double(points[3 * j + 1]),
-                                              double(points[3 * j + 2]), cb, table + int64_t(tb) * g.n_r * CH, CH, g,
-                                              out + F * b0 + (j - b0), b1 - b0);
-                    }
-                    break;
+            if (!(here && pos < o1)) {
+                if (!(a >= 0 && o0 <= pos && pos < o1)) {
+                    a = wave_search(offsets, n_atoms, pos);
+                    o0 = offsets[max(a, 0)];
+                    o1 = offsets[max(a, 0) + 1];
+                }
+                bool general = a < 0 || o0 < 0 || !(o0 <= pos && pos < o1) || o1 > n_points;  // inconsistent here
+                int ta = 0;
+                if (!general) {
+                    ta = table_of_atom ? table_of_atom[a] : a;
+                    ta = ta < 0 ? 0 : (ta >= n_tables ? n_tables - 1 : ta);
+                    // the points of this atom that fall to this workgroup from here on
+                    const int64_t left = (o1 < g1 ? o1 : g1) - pos, tile = p1 - pos;
+                    general = ta != t && (left <= tile ? left : tile + (left - tile) / group) < load_cost;
+                }
+                here = !general;
+                if (general) {
+                    const int64_t q = pos + BT < p1 ? pos + BT : p1, w0 = pos + (threadIdx.x & ~63u);
+                    if (w0 < q)
+                        proj_wave<LMAX, TIO>(centers, offsets, n_atoms, points, n_points, table, n_tables,
+                                             table_of_atom, g, out, w0, q);
+                    pos = q;
+                    continue;
                 }
                 c[0] = double(centers[3 * a]);
                 c[1] = double(centers[3 * a + 1]);
                 c[2] = double(centers[3 * a + 2]);
-                int ta = table_of_atom ? table_of_atom[a] : a;
-                ta = ta < 0 ? 0 : (ta >= n_tables ? n_tables - 1 : ta);
                 if (ta != t) {
                     t = ta;
                     __syncthreads();  // the previous table is still read
@@ -494,6 +555,7 @@ static hipError_t launch_proj_p(const ProjArgs<TIO>& A, const SplineGrid& g, siz
 // table is small (FP32 lmax <= 1: 65 us against 74 at lmax 1, 64 x 150k points).
 constexpr int kCus = 256;
 constexpr int64_t kLdsPerCu = 160 * 1024;
+constexpr int64_t kProjLoadCost = 256;  // see launch_proj_lds
 template <typename TIO, int LMAX> constexpr int kProjLdsBlock = sizeof(TIO) == 4 && LMAX <= 1 ? 512 : 1024;
 template <typename TIO> constexpr int kProjLdsMax = sizeof(TIO) == 8 ? 3 : 4;  // highest lmax that uses it
 
@@ -527,13 +589,13 @@ static hipError_t launch_proj_lds(const ProjArgs<TIO>& A, const SplineGrid& g, h
 {
     if constexpr (LMAX <= kProjLdsMax<TIO>) {
         constexpr int BT = kProjLdsBlock<TIO, LMAX>, P = kProjPpl<TIO>;
-        constexpr int64_t kTile = BT * P;
         const int groups_of = LMAX <= 2 && A.n_atoms > 128 ? 1 : 32, wgs = kCus * (1024 / BT);
-        const int64_t n_groups = wgs / groups_of, round = groups_of == 1 ? 64 : kTile;
-        const int64_t group_points = ((A.n_points + n_groups - 1) / n_groups + round - 1) / round * round;
+        const int64_t n_groups = wgs / groups_of, load_cost = kProjLoadCost + proj_lds_bytes<TIO, LMAX>(A.n_r) / 256;
+        const int64_t group_cost = (A.n_points + A.n_atoms * load_cost + n_groups - 1) / n_groups;
         hipLaunchKernelGGL((proj_lds_kernel<LMAX, TIO, P, BT>), dim3(wgs), dim3(BT),
                            size_t(proj_lds_bytes<TIO, LMAX>(A.n_r)), s, A.centers, A.offsets, A.n_atoms, A.points,
-                           A.n_points, A.table, A.n_tables, A.table_of_atom, g, A.out, group_points, groups_of);
+                           A.n_points, A.table, A.n_tables, A.table_of_atom, g, A.out, group_cost, groups_of,
+                           int(load_cost));
         return hipGetLastError();
     } else {
         return hipErrorInvalidValue;
