@@ -20,6 +20,7 @@
 namespace shk {
 
 constexpr int kFwdBlock = 256;
+constexpr int kCus = 256;  // of the GPU
 
 template <typename S, int N> struct vec_of { typedef S type __attribute__((ext_vector_type(N))); };
 template <typename S> struct vec_of<S, 1> { typedef S type; };

@@ -239,6 +239,57 @@ inline size_t proj_cap_lds(int n_atoms, int64_t n_points)
     return n_atoms > 64 || (f64 && lines) ? kCapLds2 : kCapLds1;
 }
 
+// Builds that hold tables in LDS (proj_lds_kernel): one workgroup of 1024 lanes per CU, or two
+// of 512 where the table is small (FP32 lmax <= 1: 65 us against 74 at lmax 1, 64 x 150k points).
+constexpr int64_t kLdsPerCu = 160 * 1024;
+constexpr int64_t kProjLoadCost = 256;  // a table load's worth in points, and one more per 256 bytes
+template <typename TIO, int LMAX> constexpr int kProjLdsBlock = sizeof(TIO) == 4 && LMAX <= 1 ? 512 : 1024;
+template <typename TIO> constexpr int kProjLdsMax = sizeof(TIO) == 8 ? 3 : 4;  // highest lmax that uses it
+
+template <typename TIO, int LMAX>
+constexpr int64_t proj_lds_bytes(int n_r)
+{
+    return (int64_t(n_r) * (LMAX + 1) * int64_t(sizeof(knot_t<TIO>)) + 15) / 16 * 16;
+}
+
+// Whether a large build does: the table has the build's channels (a handle keeps such copies)
+// and fits, an atom has enough points on average for its load, and over few atoms, whose
+// tables stay in the L2, there are points enough or the launch without LDS is the slower one.
+// us without / with, tables of 2000 knots: FP32 lmax 1, 64 x 17187 11.8 / 13.5, 8 x 137500 11.3 /
+// 13.2, 8 x 300000 17.0 / 18.7, 64 x 62500 36.0 / 29.9, 128 x 8593 15.7 / 14.0; FP64 lmax 0, 64 x
+// 25000 12.4 / 13.4, 64 x 62500 37.1 / 30.1, 128 x 8593 13.2 / 11.2; FP64 lmax 2, 8 x 1200000
+// 196 / 227, 64 x 150000 207 / 209, 128 x 12500 45.3 / 40.7; FP64 lmax 3, 300 x 3666 47.2 / 58.2,
+// 300 x 5333 65.9 / 64.9; FP32 lmax 3, 64 x 62500 72.2 / 70.9, 300 x 5333 41.1 / 40.3.
+template <typename TIO, int LMAX>
+inline bool use_proj_lds(int n_atoms, int64_t n_points, int tab_ch, int n_r)
+{
+    constexpr bool f64 = sizeof(TIO) == 8;
+    if (LMAX > kProjLdsMax<TIO> || tab_ch != LMAX + 1) return false;
+    if (proj_lds_bytes<TIO, LMAX>(n_r) * (1024 / kProjLdsBlock<TIO, LMAX>) > kLdsPerCu) return false;
+    if (n_points < kProjVecPoints || n_points / (f64 && LMAX == 3 ? 4096 : 2048) < n_atoms) return false;
+    if (LMAX == (f64 ? 1 : 2)) return true;
+    if (LMAX == 0 || (!f64 && LMAX == 1)) return n_atoms > 64 || n_points >= int64_t(3) << 20;
+    return n_atoms > (f64 && LMAX == 3 ? 128 : 64);
+}
+
+// How many workgroups go side by side through consecutive points there: 1, or the 32 CUs of an
+// XCD where the write path is what counts and the points are enough for 32 loads of a table.
+// us with 1 / 32: FP32 lmax 0, 64 x 150000 37.7 / 39.2; lmax 1, 64 x 62500 29.9 / 32.7, 64 x
+// 150000 into one output 66.8 / 63.3, 128 x 18750 18.9 / 24.7; lmax 2, 64 x 37500 32.5 / 38.5, 64 x
+// 150000 116 / 109; lmax 3, 300 x 3666 30.7 / 37.8, 300 x 5333 36.6 / 40.1, 128 x 31250 82.1 /
+// 70.8; FP64 lmax 0, 8 x 1200000 68.1 / 63.3, 64 x 150000 69.1 / 66.6, 128 x 75000 67.7 / 83.2;
+// lmax 1, 8 x 137500 15.4 / 16.5, 64 x 150000 128 / 122, 128 x 75000 128 / 143; lmax 2, 128 x
+// 12500 40.7 / 41.5, 300 x 3666 37.1 / 42.5; lmax 3, 300 x 13333 168 / 159.
+template <typename TIO, int LMAX>
+inline int proj_lds_group(int n_atoms, int64_t n_points)
+{
+    constexpr bool f64 = sizeof(TIO) == 8;
+    constexpr int kAtoms = LMAX > 2 ? 1 << 30 : (!f64 && LMAX == 2 ? 128 : 64);  // at most, for 32
+    constexpr int kLog = LMAX == (f64 ? 0 : 1) ? 23 : (f64 ? 21 : (LMAX == 2 ? 22 : 21));
+    if (LMAX == (f64 ? 2 : 0)) return 1;
+    return n_atoms <= kAtoms && ((f64 && LMAX == 3) || n_points >= int64_t(1) << kLog) ? 32 : 1;
+}
+
 // Wave-wide searches, N at once over the same n sorted keys: at[i] = the last k in [0, n)
 // with key(k) <= x[i], or -1 if there is none.  Every lane must be active and pass the same
 // x; each round the 64 lanes probe 64 evenly spaced keys and a ballot keeps the bracket, so

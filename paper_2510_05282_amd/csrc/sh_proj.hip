@@ -19,6 +19,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "sh_core.h"
 #include "sh_internal.h"
 #include "sh_proj.h"
@@ -392,6 +394,12 @@ __device__ __forceinline__ void proj_wave(const TIO* __restrict__ centers, const
                           out + nfun(LMAX) * o0 + (j - o0), o1 - o0);
 }
 
+// A workgroup's points, and the atom at their beginning with its own.
+struct ProjShare {
+    int64_t begin, end, o0, o1;
+    int a;
+};
+
 // Persistent build for small lmax: a workgroup keeps the spline table of the atom it works
 // on in LDS (of LMAX + 1 channels) and walks tiles of BT * PPL points.  A lookup
 // scatters its lanes over as many cache lines, one tag check each: at lmax 3 in FP32 two
@@ -422,35 +430,45 @@ __global__ __launch_bounds__(BT) void proj_lds_kernel(const TIO* __restrict__ ce
                                                       const knot_t<TIO>* __restrict__ table,
                                                       int n_tables, const int32_t* __restrict__ table_of_atom,
                                                       SplineGrid g, TIO* __restrict__ out, int64_t group_cost,
-                                                      int group, int load_cost)
+                                                      int group_log, int load_cost)
 {
     using KN = knot_t<TIO>;
     constexpr int F = nfun(LMAX), CH = LMAX + 1;
     extern __shared__ __align__(16) unsigned char lds[];
     KN* tab = reinterpret_cast<KN*>(lds);
     const uint32_t w = xcd_tile(blockIdx.x, gridDim.x);
-    // the group's share: load_cost units before each atom's points, one for each of them
-    const int64_t gi = w / group, cost = n_points + int64_t(n_atoms) * load_cost;
-    const int64_t x[2] = {gi * group_cost, (gi + 1) * group_cost};
-    int at[2];
-    wave_searches<2>(n_atoms, [&](int k) { return offsets[k] + int64_t(k) * load_cost; }, x, at);
-    int64_t from[2], till[2], begin[2];  // the atom that each end of the share lies in, and where
+    // The group's share: load_cost units before each atom's points, one for each of them.  One
+    // wave finds it for all (every wave doing so took 1 us of a build's 12).
+    ProjShare& share = *reinterpret_cast<ProjShare*>(lds);
+    if (threadIdx.x < 64) {
+        const int64_t gi = w >> group_log, cost = n_points + int64_t(n_atoms) * load_cost;
+        const int64_t x[2] = {gi * group_cost, (gi + 1) * group_cost};
+        int at[2];
+        wave_searches<2>(n_atoms, [&](int k) { return offsets[k] + int64_t(k) * load_cost; }, x, at);
+        int64_t from[2], till[2], end[2];  // the atom that each end of the share lies in, and where
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int b = max(at[i], 0);
-        from[i] = offsets[b];
-        till[i] = offsets[b + 1];
-        const int64_t in = x[i] - (from[i] + (int64_t(b) + 1) * load_cost);
-        const int64_t p = in <= 0 ? from[i] : (in < till[i] - from[i] ? from[i] + in / 64 * 64 : till[i]);
-        begin[i] = x[i] >= cost ? n_points : (p < 0 || x[i] == 0 ? 0 : (p < n_points ? p : n_points));
+        for (int i = 0; i < 2; ++i) {
+            const int b = max(at[i], 0);
+            from[i] = offsets[b];
+            till[i] = offsets[b + 1];
+            // no share begins or ends within an atom's first or last points that are too few for a load
+            const int64_t in = x[i] - (from[i] + (int64_t(b) + 1) * load_cost);
+            const int64_t p = in < load_cost                       ? from[i]
+                              : in < till[i] - from[i] - load_cost ? from[i] + in / 64 * 64
+                                                                   : till[i];
+            end[i] = x[i] >= cost ? n_points : (p < 0 || x[i] == 0 ? 0 : (p < n_points ? p : n_points));
+        }
+        if (threadIdx.x == 0) share = ProjShare{end[0], end[1], from[0], till[0], at[0]};
     }
-    const int64_t g0 = begin[0], g1 = begin[1];
-    int a = at[0];                          // the atom looked at last
-    int64_t o0 = from[0], o1 = till[0];     // its points
+    __syncthreads();
+    const int64_t g0 = lane_value(share.begin, 0), g1 = lane_value(share.end, 0);
+    int64_t o0 = lane_value(share.o0, 0), o1 = lane_value(share.o1, 0);  // the points of
+    int a = lane_value(share.a, 0);                                      // the atom looked at last
     bool here = false;                      // whether it is the current one
     int t = -1;                             // the table held in LDS
     double c[3] = {};
-    for (int64_t p0 = g0 + int64_t(w % group) * (BT * PPL); p0 < g1; p0 += int64_t(group) * (BT * PPL)) {
+    const uint32_t wi = w & ((1u << group_log) - 1);
+    for (int64_t p0 = g0 + int64_t(wi) * (BT * PPL); p0 < g1; p0 += int64_t(BT * PPL) << group_log) {
         const int64_t p1 = p0 + BT * PPL < g1 ? p0 + BT * PPL : g1;
         int64_t pos = p0;
         while (pos < p1) {
@@ -467,7 +485,7 @@ __global__ __launch_bounds__(BT) void proj_lds_kernel(const TIO* __restrict__ ce
                     ta = ta < 0 ? 0 : (ta >= n_tables ? n_tables - 1 : ta);
                     // the points of this atom that fall to this workgroup from here on
                     const int64_t left = (o1 < g1 ? o1 : g1) - pos, tile = p1 - pos;
-                    general = ta != t && (left <= tile ? left : tile + (left - tile) / group) < load_cost;
+                    general = ta != t && (left <= tile ? left : tile + ((left - tile) >> group_log)) < load_cost;
                 }
                 here = !general;
                 if (general) {
@@ -483,7 +501,7 @@ __global__ __launch_bounds__(BT) void proj_lds_kernel(const TIO* __restrict__ ce
                 c[2] = double(centers[3 * a + 2]);
                 if (ta != t) {
                     t = ta;
-                    __syncthreads();  // the previous table is still read
+                    __syncthreads();  // the previous table, or the share, is still read
                     const KN* src = table + int64_t(t) * g.n_r * CH;
                     typedef float v4 __attribute__((ext_vector_type(4), aligned(8)));  // a float pair's
                     const int n16 = int(g.n_r * CH * sizeof(KN) / 16);
@@ -538,9 +556,9 @@ static hipError_t launch_proj_p(const ProjArgs<TIO>& A, const SplineGrid& g, siz
         const int64_t nc = A.n_points - j0 < kProjChunk ? A.n_points - j0 : kProjChunk;
         const dim3 grid = dim3(unsigned((nc + 256 * P - 1) / (256 * P))), block = dim3(256);
         if (kProjSmall<P, LMAX> && A.n_atoms <= 64)
-            hipLaunchKernelGGL((proj_kernel<LMAX, TIO, P, kProjSmall<P, LMAX>>), grid, block, lds, s, A.centers, A.offsets,
-                               A.n_atoms, A.points, A.n_points, A.table, A.tab_ch, A.n_tables, A.table_of_atom, g,
-                               A.out, j0);
+            hipLaunchKernelGGL((proj_kernel<LMAX, TIO, P, kProjSmall<P, LMAX>>), grid, block, lds, s, A.centers,
+                               A.offsets, A.n_atoms, A.points, A.n_points, A.table, A.tab_ch, A.n_tables,
+                               A.table_of_atom, g, A.out, j0);
         else
             hipLaunchKernelGGL((proj_kernel<LMAX, TIO, P, false>), grid, block, lds, s, A.centers, A.offsets,
                                A.n_atoms, A.points, A.n_points, A.table, A.tab_ch, A.n_tables, A.table_of_atom, g,
@@ -551,50 +569,17 @@ static hipError_t launch_proj_p(const ProjArgs<TIO>& A, const SplineGrid& g, siz
     return hipSuccess;
 }
 
-// proj_lds_kernel's launch: one workgroup of 1024 lanes per CU, or two of 512 where the
-// table is small (FP32 lmax <= 1: 65 us against 74 at lmax 1, 64 x 150k points).
-constexpr int kCus = 256;
-constexpr int64_t kLdsPerCu = 160 * 1024;
-constexpr int64_t kProjLoadCost = 256;  // see launch_proj_lds
-template <typename TIO, int LMAX> constexpr int kProjLdsBlock = sizeof(TIO) == 4 && LMAX <= 1 ? 512 : 1024;
-template <typename TIO> constexpr int kProjLdsMax = sizeof(TIO) == 8 ? 3 : 4;  // highest lmax that uses it
-
-template <typename TIO, int LMAX>
-static int64_t proj_lds_bytes(int n_r)
-{
-    return (int64_t(n_r) * (LMAX + 1) * int64_t(sizeof(knot_t<TIO>)) + 15) / 16 * 16;
-}
-
-// Whether a large build takes proj_lds_kernel (both sides measured, see there): the table
-// has the build's channels (a handle keeps such copies) and fits, an atom has enough
-// points on average for its load, and where the launch without LDS is as fast over few
-// atoms, the atoms or the points are many.
-template <typename TIO, int LMAX>
-static bool use_proj_lds(const ProjArgs<TIO>& A)
-{
-    constexpr bool f64 = sizeof(TIO) == 8;
-    if (LMAX > kProjLdsMax<TIO> || A.tab_ch != LMAX + 1) return false;
-    if (proj_lds_bytes<TIO, LMAX>(A.n_r) * (1024 / kProjLdsBlock<TIO, LMAX>) > kLdsPerCu) return false;
-    if (A.n_points < kProjVecPoints || A.n_points / 2048 < A.n_atoms) return false;
-    if (f64) {
-        if (LMAX == 0) return A.n_atoms > 128 || A.n_points >= int64_t(1) << 23;
-        if (LMAX == 2) return A.n_atoms > 64 || A.n_points >= int64_t(1) << 22;
-        return LMAX == 1 || A.n_atoms > 128;
-    }
-    return LMAX <= 2 || A.n_atoms > 64;
-}
-
 template <int LMAX, typename TIO>
 static hipError_t launch_proj_lds(const ProjArgs<TIO>& A, const SplineGrid& g, hipStream_t s)
 {
     if constexpr (LMAX <= kProjLdsMax<TIO>) {
         constexpr int BT = kProjLdsBlock<TIO, LMAX>, P = kProjPpl<TIO>;
-        const int groups_of = LMAX <= 2 && A.n_atoms > 128 ? 1 : 32, wgs = kCus * (1024 / BT);
-        const int64_t n_groups = wgs / groups_of, load_cost = kProjLoadCost + proj_lds_bytes<TIO, LMAX>(A.n_r) / 256;
+        const int group_log = proj_lds_group<TIO, LMAX>(A.n_atoms, A.n_points) == 1 ? 0 : 5, wgs = kCus * (1024 / BT);
+        const int64_t n_groups = wgs >> group_log, load_cost = kProjLoadCost + proj_lds_bytes<TIO, LMAX>(A.n_r) / 256;
         const int64_t group_cost = (A.n_points + A.n_atoms * load_cost + n_groups - 1) / n_groups;
         hipLaunchKernelGGL((proj_lds_kernel<LMAX, TIO, P, BT>), dim3(wgs), dim3(BT),
-                           size_t(proj_lds_bytes<TIO, LMAX>(A.n_r)), s, A.centers, A.offsets, A.n_atoms, A.points,
-                           A.n_points, A.table, A.n_tables, A.table_of_atom, g, A.out, group_cost, groups_of,
+                           std::max(size_t(proj_lds_bytes<TIO, LMAX>(A.n_r)), sizeof(ProjShare)), s, A.centers, A.offsets, A.n_atoms, A.points,
+                           A.n_points, A.table, A.n_tables, A.table_of_atom, g, A.out, group_cost, group_log,
                            int(load_cost));
         return hipGetLastError();
     } else {
@@ -608,7 +593,7 @@ static hipError_t launch_proj_l(const ProjArgs<TIO>& A, hipStream_t s)
     const SplineGrid g{A.n_r, A.h, 1.0 / A.h, A.r_max, A.h * A.h / 6.0};
     if (A.n_points < kProjVecPoints && A.n_points * nfun(LMAX) * int64_t(sizeof(TIO)) < kProjVecBytes)
         return launch_proj_p<LMAX, TIO, 1>(A, g, 0, s);
-    if (use_proj_lds<TIO, LMAX>(A)) return launch_proj_lds<LMAX, TIO>(A, g, s);
+    if (use_proj_lds<TIO, LMAX>(A.n_atoms, A.n_points, A.tab_ch, A.n_r)) return launch_proj_lds<LMAX, TIO>(A, g, s);
     return launch_proj_p<LMAX, TIO, kProjPpl<TIO>>(A, g, proj_cap_lds<TIO, LMAX>(A.n_atoms, A.n_points), s);
 }
 
