@@ -6,8 +6,8 @@
 // flops, so it is bound by HBM stores.  Launch choices, all measured on MI355X:
 //  - Each lane evaluates 16 bytes' worth of adjacent points (two in FP64, four
 //    in FP32) and stores 16 bytes per row, at any element alignment: one contiguous
-//    1 KiB run per wave and row.  Outputs below kFwdVecBytes take one point per lane:
-//    they stay in the caches on the way out, and what such a launch lasts is its
+//    1 KiB run per wave and row.  Outputs that stay in the caches on the way out, and
+//    launches of few workgroups, take one point per lane: what they last is their
 //    workgroups' chain of work, which the wider lanes lengthen.
 //  - Workgroups are remapped so each XCD walks one contiguous range of points.
 //  - The kernels of large outputs reserve LDS they do not use, which caps the
@@ -63,12 +63,18 @@ static hipError_t launch_fwd_l(int64_t n, Inputs<MODE, TIO> in, TIO* out, int64_
     // store_shape never asks lmax 1 for more than one point per lane
     constexpr bool kBusy = MODE == In::kAngles && LMAX <= 6;
     constexpr int kVec = LMAX == 1 && !kBusy ? 1 : 16 / sizeof(TIO);
-    StoreShape f = store_shape<nfun(LMAX), TIO>(n * nfun(LMAX) * int64_t(sizeof(TIO)), on_lines(out, ld * sizeof(TIO)));
+    const int64_t bytes = n * nfun(LMAX) * int64_t(sizeof(TIO));
+    const bool lines = on_lines(out, ld * sizeof(TIO));
+    StoreShape f = store_shape<nfun(LMAX), TIO>(n, sizeof(TIO), MODE == In::kAngles ? 0 : 3 * sizeof(TIO), lines);
     // angles take two FP64 sines and cosines per point, which at few rows need every wave
     // (us, wide uncapped / capped / one point: FP64 lmax 2, 8000000 points 137 / 180 / 135; lmax 3,
     // 1500000 43.4 / 48.0 / 45.6; FP32 lmax 1, 9000001 64 / 86 / 94; lmax 6, 1000001 43.4 /
-    // 45.9 / 52.4)
-    if (kBusy && n * nfun(LMAX) * int64_t(sizeof(TIO)) >= kWideBytes) f = {LMAX != 2 || sizeof(TIO) == 4, 0};
+    // 45.9 / 52.4), and at more rows until the output is far from the caches (FP32 lmax 7, 585857
+    // points 31.1 / 35.4 / 30.5, 859265 48.9 / 51.1 / 56.5, 1562497 89.9 / 87.7 / 117; FP64 lmax 9,
+    // 187392 28.9 / 30.0 / 28.2)
+    if (kBusy && bytes >= kWideBytes) f = {LMAX != 2 || sizeof(TIO) == 4, 0};
+    if (MODE == In::kAngles && LMAX > 6 && bytes < 2 * kWideBytes && (!lines || bytes < kOffBytes))
+        f = {bytes >= kOffBytes, 0};
     // angles may be rows of out, as every point's are read before its values are written:
     // then no lane reads a neighbour's, and a remainder takes one point per lane
     const bool in_place = in.shares(out, n, (nfun(LMAX) - 1) * ld + n);
@@ -152,9 +158,15 @@ static hipError_t launch_complex_l(int64_t n, AnyInputs<TIO> in, TIO* out, int64
 {
     constexpr int kRows = (SPINOR ? 4 : 1) * nfun(LMAX);
     constexpr int kVec = sizeof(TIO) == 4 && kRows != 4 ? 2 : 1;  // store_shape never asks 4 rows for more
-    constexpr int64_t kValue = 2 * sizeof(TIO);
-    StoreShape f = store_shape<kRows, TIO>(n * kRows * kValue, on_lines(out, ld * kValue));
-    if (in.mode == In::kAngles && kRows <= 16) f.lds = 0;  // as for the real harmonics of angles
+    constexpr int kValue = 2 * sizeof(TIO);
+    StoreShape f = store_shape<kRows, TIO>(n, kValue, 0, on_lines(out, ld * kValue));
+    // angles need every wave, as for the real harmonics: below 2^29 bytes at any number of rows
+    // (us, uncapped / one workgroup per CU: FP64 lmax 4, 374913 points 28.5 / 32.7, lmax 7, 214785
+    // 47.8 / 50.2; FP32 lmax 4, 1000001 42.5 / 48.5), above at few; but FP64 at 16 and 25 rows from
+    // 5 x 2^26 bytes on two workgroups per CU (spinor lmax 1, 1562497 uncapped 93.6, so 90.2, 2343681
+    // 147 / 134; lmax 4, 1499905 135 / 130)
+    if (in.mode == In::kAngles && (kRows <= 25 || n * kRows * kValue < kCapBytes))
+        f.lds = kRows >= 16 && kRows <= 25 && sizeof(TIO) == 8 && n * kRows * kValue >= 2 * kOffBytes ? kCapLds2 : 0;
     for (int64_t c0 = 0; c0 < n; c0 += kChunk) {
         const int64_t nc = n - c0 < kChunk ? n - c0 : kChunk;
         const hipError_t e = f.wide && nc >= kVec

@@ -52,43 +52,69 @@ inline bool on_lines(const void* p, int64_t row_bytes)
     return row_bytes % 128 == 0 && reinterpret_cast<uintptr_t>(p) % 128 == 0;
 }
 
-// The shape of a launch that writes ROWS rows and `bytes` in all, for the real, complex
-// and spinor harmonics and the Jacobian.  Small outputs stay in the caches on their way
-// out, and such a launch lasts its workgroups' chain of work, which wide lanes lengthen;
-// large ones are bound by the HBM write path, which rewards wide stores and, from 16
-// rows on, few waves at once: the writes under way to each row then lie in a smaller
-// window, and the partial lines that neighbouring waves write where rows do not start on
-// lines merge in the L2.  Measured in us as points per lane / KiB reserved, 3 inputs and
-// outputs in turn (n odd means rows off the lines):
-//  below 2^27 bytes    FP64 lmax 6, 2^18 points (103 MB) 1/0 18.6, 2/54 18.9; FP32 lmax 3,
-//                      2^20 (67 MB) 1/0 12.7, 4/54 13.5; FP32 lmax 9, 2^17 1/0 9.7, 4/54
-//                      10.8; complex FP64 lmax 9, 50001 1/0 13.7, 2/0 21.6
-//  1 row               FP32 2^25 points 4/0 22.1, 4/54 22.8, 1/0 32.0; FP64 equal
+// The shape of a launch over n points that writes ROWS rows of `value` bytes a point, for the
+// real, complex and spinor harmonics and the Jacobian; in_bytes a point are read (0: not
+// counted).  Small outputs stay in the caches on their way out, and such a launch lasts its
+// workgroups' chain of work, which wide lanes lengthen; large ones are bound by the HBM write
+// path, which rewards wide stores and, from 16 rows on, few waves at once: the writes under way
+// to each row then lie in a smaller window, and the partial lines that neighbouring waves write
+// where rows do not start on lines merge in the L2.  Measured in us as points per lane / KiB
+// reserved, two or three outputs in turn, "odd" where rows lie off the lines:
+//  one round           a launch of one point per lane that the CUs hold in one round halves
+//                      its workgroups with two: Jacobian lmax 9, 42368 points 1/0 27.8, 2/0 28.7,
+//                      60032 37.1 / 38.3, odd 45001 31.5 / 31.8, 66048 46.4 / 41.3; FP32 spinor lmax
+//                      8, 56064 28.0 / 29.5
+//  1 row               FP32 15M points 4/0 10.3, 4/54 12.4, 1/0 16.6, 25M 16.2, 18.2, 25.1, 4M 6.9,
+//                      6.9, 7.4; FP64 7.5M 2/0 10.3, 1/0 11.0
 //  4 rows              2^25 points FP64 1/40 307, 1/0 328, 2/54 321; FP32 1/0 156, 4/54
 //                      184; complex 8000001 FP64 1/40 126, 1/54 155, FP32 1/0 67, 2/54 86
+//  below 2^27 bytes    FP64 lmax 6, 255000 points (100 MB) 1/0 19.1, 2/54 19.6; FP32 lmax 5,
+//                      798592 (115 MB) 24.4, 24.8; lmax 9, 2^17 9.7, 10.8; complex FP64 lmax 9,
+//                      50001 1/0 13.7, 2/0 21.6
+//  read and written    on lines it is what is read and written that leaves the caches: 9 rows
+//                      FP64 115 MB written 1/0 30.6, 2/54 29.7, 133 MB 38.5, 37.1, 100 MB 20.1, 20.9; 16
+//                      rows FP64 133 MB 1/0 33.9, 2/0 29.5, FP32 34.2, 4/54 32.0; 25 rows FP32 133 MB
+//                      30.0, 4/54 26.2; 36 rows FP64 133 MB 24.8, 22.9; Jacobian lmax 2 133 MB 23.6, 22.6
 //  9 rows              2^25 points FP64 2/54 563, 2/0 608, 2/84 582; FP32 4/54 283, 4/84
 //                      324; complex 8000001 FP32 2/54 127, 1/0 141, 2/84 156
-//  16 rows and more    n odd: FP64 lmax 9, 2^22 + 1 points 2/84 661, 2/54 748, 2/0 783, 1/0
-//                      857; FP32 lmax 8, 2^23 + 3 4/84 532, 4/54 594, 1/0 820; complex lmax 9,
-//                      1000001 FP64 1/84 328, 1/54 337, FP32 2/84 166, 1/0 191; Jacobian lmax
-//                      9, 1000001 2/84 651, 2/54 708, 1/0 813; n = 1000002 (16- but not
-//                      128-byte aligned) FP64 lmax 9 2/84 164, 2/0 177
-//  the same on lines,  below 2^29 bytes: FP64 lmax 9, 2^19 2/0 77.2, 2/84 80.4; FP32 lmax
-//                      5, 2^21 4/0 61.3, 4/84 63.6; complex FP64 lmax 6, 250000 1/0 38.0,
-//                      1/54 39.3.  Above: FP64 lmax 3, 2^25 2/84 875, 2/54 910, lmax 4 1386,
-//                      1375, lmax 9 at 2^26 68.4% of 8 TB/s against 67.8%; Jacobian lmax 8
-//                      (324 rows), 703552 345 / 342; FP32 equal
-constexpr int64_t kWideBytes = int64_t(1) << 27, kCapBytes = int64_t(1) << 29;
+//  on lines,           below 2^29 bytes: FP64 lmax 9, 2^19 2/0 77.2, 2/84 80.4; FP32 lmax
+//  16 rows and more    5, 2^21 4/0 61.3, 4/84 63.6; complex FP64 lmax 6, 250000 1/0 38.0,
+//                      1/54 39.3, but FP32 lmax 3, 180 MB 4/0 43.5, 4/54 42.2, into one output 33.8,
+//                      32.2.  Above: 16 rows FP64 800 MB 2/84 178, 2/54 184, FP32 173, 183, complex
+//                      lmax 3 FP32 164, 173, FP64 168, 172, spinor lmax 1 165, 173 and 168, 171, Jacobian
+//                      lmax 1 180, 183; FP64 lmax 4, 2^25 points 1386, 1375, lmax 9 at 2^26 68.4% of
+//                      8 TB/s against 67.8%, but complex FP64 lmax 9, 560 MB 111, 108, FP32 equal
+//  off the lines,      below 5 x 2^25 bytes: FP64 lmax 7, 137 MB 1/0 23.4, 2/0 23.9, 2/84 26.0, lmax
+//  16 rows and more    5, 150 MB 37.8, 32.6, 36.5; FP32 lmax 7 137 MB 24.6, 24.7, 27.5; complex FP64
+//                      lmax 3, 137 MB 1/0 25.9, 1/84 30.9; FP32 spinor lmax 1 28.6, 27.2, 30.3; but
+//                      FP64 lmax 3, 150 MB 42.0, 39.1, 38.8, of three outputs 41.5, 41.4, 37.0, FP32
+//                      lmax 3 43.9, 39.4, 4/54 39.6, of one 27.1, 29.0, 4/54 27.3.  Above: FP64 lmax
+//                      3, 220 MB 2/84 50.0, 2/0 57.5, lmax 9, 2^22 + 1 points 661, 783, 2/54 748;
+//                      FP32 lmax 8, 2^23 + 3 4/84 532, 4/54 594, 1/0 820; complex lmax 9, 1000001
+//                      FP64 1/84 328, 1/54 337, FP32 2/84 166, 1/0 191; Jacobian lmax 9, 1000001
+//                      2/84 651, 2/54 708, 1/0 813
+// A caller that writes one output again and again, below 220 MB, is served by the memory-side
+// cache, where off the lines one point per lane stays ahead by 1 to 5% (FP64 lmax 3, 150 MB
+// 26.6 / 27.4, FP32 lmax 4 25.4 / 26.7); the lines are drawn for two outputs in turn, as
+// a new output for every call makes them.
+constexpr int64_t kWideBytes = int64_t(1) << 27, kOffBytes = int64_t(5) << 25, kCapBytes = int64_t(1) << 29;
+constexpr int64_t kOneRound = int64_t(kCus) * kFwdBlock;
 
 template <int ROWS, typename TIO>
-inline StoreShape store_shape(int64_t bytes, bool lines)
+inline StoreShape store_shape(int64_t n, int value, int in_bytes, bool lines)
 {
-    if (bytes < kWideBytes) return {false, 0};
-    if (ROWS == 1) return {true, 0};
-    if (ROWS <= 4) return {false, sizeof(TIO) == 8 ? kCapLds4 : 0};
+    const int64_t bytes = n * ROWS * value;
+    if (ROWS == 1) return {bytes >= kWideBytes / 16, 0};
+    if (ROWS <= 4) return {false, sizeof(TIO) == 8 && bytes >= kWideBytes ? kCapLds4 : 0};
+    if (n <= kOneRound || bytes + (lines && ROWS <= 49 ? n * in_bytes : 0) < kWideBytes) return {false, 0};
     if (ROWS <= 9) return {true, kCapLds2};
-    if (lines && bytes < kCapBytes) return {true, 0};
-    return {true, !lines || ROWS == 16 || (ROWS > 64 && ROWS <= 100 && sizeof(TIO) == 8) ? kCapLds1 : kCapLds2};
+    const bool real = value == int(sizeof(TIO)), one16 = ROWS == 16 && real && sizeof(TIO) == 8;
+    if (bytes < (lines ? kCapBytes : (one16 ? 0 : kOffBytes))) {
+        const bool two = real && sizeof(TIO) == 4 && (ROWS == 16 || (ROWS == 25 && lines && bytes < kWideBytes));
+        return {true, two ? kCapLds2 : 0};
+    }
+    return {true, !lines || ROWS == 16 || (ROWS > 64 && ROWS <= 100 && value == 8 && sizeof(TIO) == 8) ? kCapLds1
+                                                                                                      : kCapLds2};
 }
 
 // First point of lane `t` of a launch whose lanes take PPL adjacent points of n >= PPL

@@ -178,7 +178,7 @@ static hipError_t launch_jac_l(int64_t n, const double* xyz, double* out, double
 {
     constexpr int kRows = 4 * nfun(LMAX);
     constexpr int kVec = kRows == 4 ? 1 : 2;  // store_shape never asks 4 rows for more
-    const StoreShape f = store_shape<kRows, double>(n * kRows * int64_t(sizeof(double)),
+    const StoreShape f = store_shape<kRows, double>(n, sizeof(double), 3 * sizeof(double),
                                                     on_lines(out, ld * 8) && on_lines(jac, ld * 8));
     for (int64_t c0 = 0; c0 < n; c0 += kGradChunk) {
         const int64_t nc = n - c0 < kGradChunk ? n - c0 : kGradChunk;

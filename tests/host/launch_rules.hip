@@ -29,3 +29,29 @@ extern "C" int rule_proj_lds(int f64, int lmax, int n_atoms, long n_points, int 
     return f64 ? proj_lds_of<double>(lmax, n_atoms, n_points, tab_ch, n_r)
                : proj_lds_of<float>(lmax, n_atoms, n_points, tab_ch, n_r);
 }
+
+// KiB of LDS reserved, plus 1000 where lanes take several points.
+template <int ROWS>
+static int store(int f64, int64_t n, int value, int in_bytes, int lines)
+{
+    const shk::StoreShape s = f64 ? shk::store_shape<ROWS, double>(n, value, in_bytes, lines)
+                                  : shk::store_shape<ROWS, float>(n, value, in_bytes, lines);
+    return (s.wide ? 1000 : 0) + int(s.lds / 1024);
+}
+
+extern "C" int rule_store(int rows, int f64, long n, int value, int in_bytes, int lines)
+{
+    switch (rows) {
+    case 1: return store<1>(f64, n, value, in_bytes, lines);
+    case 4: return store<4>(f64, n, value, in_bytes, lines);
+    case 9: return store<9>(f64, n, value, in_bytes, lines);
+    case 16: return store<16>(f64, n, value, in_bytes, lines);
+    case 25: return store<25>(f64, n, value, in_bytes, lines);
+    case 36: return store<36>(f64, n, value, in_bytes, lines);
+    case 64: return store<64>(f64, n, value, in_bytes, lines);
+    case 100: return store<100>(f64, n, value, in_bytes, lines);
+    case 324: return store<324>(f64, n, value, in_bytes, lines);
+    case 400: return store<400>(f64, n, value, in_bytes, lines);
+    default: return -1;
+    }
+}

@@ -23,15 +23,18 @@ def rules(tmp_path_factory):
                            os.path.join(ROOT, "tests", "host", "launch_rules.hip"), "-o", so],
                           stderr=subprocess.DEVNULL)
     L = ctypes.CDLL(so)
+    L.rule_store.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int, ctypes.c_int, ctypes.c_int]
     L.rule_proj_lds.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int, ctypes.c_int]
     return L
 
 
 @pytest.mark.parametrize("f64,lmax,atoms,points,group", [
     (0, 1, 64, 17187, 0), (0, 1, 8, 137500, 0), (0, 1, 8, 300000, 0), (0, 0, 64, 25000, 0), (0, 1, 64, 62500, 1),
-    (0, 1, 64, 150000, 32), (0, 1, 128, 8593, 1), (0, 1, 128, 18750, 1), (0, 0, 128, 18750, 1), (0, 2, 128, 8593, 1), (0, 2, 64, 150000, 32),
+    (0, 1, 64, 150000, 32), (0, 1, 128, 8593, 1), (0, 1, 128, 18750, 1), (0, 0, 128, 18750, 1), (0, 2, 128, 8593, 1),
+    (0, 2, 64, 150000, 32),
     (0, 3, 300, 3666, 1), (0, 4, 300, 3666, 1), (0, 4, 128, 8593, 1), (0, 3, 128, 31250, 32), (0, 3, 64, 150000, 0),
-    (1, 0, 64, 25000, 0), (1, 0, 64, 62500, 1), (1, 0, 64, 150000, 32), (1, 0, 128, 75000, 1), (1, 1, 8, 137500, 1), (1, 1, 64, 150000, 32),
+    (1, 0, 64, 25000, 0), (1, 0, 64, 62500, 1), (1, 0, 64, 150000, 32), (1, 0, 128, 75000, 1), (1, 1, 8, 137500, 1),
+    (1, 1, 64, 150000, 32),
     (1, 1, 128, 75000, 1), (1, 2, 8, 1200000, 0), (1, 2, 64, 150000, 0), (1, 2, 300, 3666, 1), (1, 3, 300, 3666, 0),
     (1, 3, 300, 5333, 32), (1, 3, 64, 150000, 0)])
 def test_builds_with_tables_in_lds(rules, f64, lmax, atoms, points, group):
@@ -44,3 +47,33 @@ def test_tables_that_fit(rules, f64, lmax, knots):
     assert rules.rule_proj_lds(f64, lmax, 200, 200 * 20000, lmax + 1, knots) > 0
     assert rules.rule_proj_lds(f64, lmax, 200, 200 * 20000, lmax + 1, knots + 1) == 0
     assert rules.rule_proj_lds(f64, lmax, 200, 200 * 20000, lmax + 2, 300) == 0  # more channels than the build's
+
+
+ONE, WIDE = 0, 1000  # points per lane; plus the KiB reserved
+
+
+@pytest.mark.parametrize("rows,f64,n,value,reads,lines,shape", [
+    # the CUs hold all workgroups of a launch of one point per lane at once (Jacobian, spinor)
+    (400, 1, 42368, 8, 24, 1, ONE), (400, 1, 65536, 8, 24, 1, ONE), (400, 1, 45001, 8, 24, 0, ONE),
+    (400, 1, 66048, 8, 24, 1, WIDE), (324, 0, 56064, 8, 0, 1, ONE), (324, 0, 66048, 8, 0, 1, WIDE),
+    # one row, at every size that fills the GPU
+    (1, 0, 25_000_000, 4, 12, 1, WIDE), (1, 0, 33_249_921, 4, 12, 0, WIDE), (1, 0, 1 << 20, 4, 12, 1, ONE),
+    (1, 1, 7_499_904, 8, 24, 1, WIDE),
+    # on lines, what is read counts: 115 to 134 MB written at few rows
+    (9, 1, 1_597_184, 8, 24, 1, WIDE + 54), (9, 1, 1_388_672, 8, 24, 1, ONE),
+    (16, 0, 2_078_080, 4, 12, 1, WIDE + 54),
+    (16, 1, 1_038_976, 8, 24, 1, WIDE), (25, 0, 1_329_920, 4, 12, 1, WIDE + 54), (36, 1, 461_696, 8, 24, 1, WIDE),
+    (36, 1, 461_697, 8, 24, 0, ONE), (36, 1, 399_232, 8, 24, 1, ONE), (64, 1, 259_712, 8, 24, 1, ONE),
+    # FP32 lmax 3 on lines keeps two workgroups per CU
+    (16, 0, 2_812_416, 4, 12, 1, WIDE + 54), (16, 0, 1_171_840, 8, 0, 1, WIDE), (16, 1, 1_406_208, 8, 24, 1, WIDE),
+    # off the lines, uncapped below 5 x 2^25 bytes, then one workgroup per CU
+    (64, 1, 292_865, 8, 24, 0, WIDE), (16, 1, 535_169, 16, 0, 0, WIDE), (64, 1, 429_569, 8, 24, 0, WIDE + 84),
+    (9, 1, 2_083_329, 8, 24, 0, WIDE + 54), (16, 1, 1_171_841, 8, 24, 0, WIDE + 84),
+    (16, 0, 2_343_681, 4, 12, 0, WIDE + 54), (25, 0, 1_499_905, 4, 12, 0, WIDE),
+    # large and on lines
+    (16, 0, 12_499_968, 4, 12, 1, WIDE + 84), (16, 1, 5_078_016, 16, 0, 1, WIDE + 84),
+    (100, 1, 999_936, 8, 24, 1, WIDE + 84), (100, 1, 499_968, 16, 0, 1, WIDE + 54),
+    (25, 1, 1 << 25, 8, 24, 1, WIDE + 54),
+    (4, 1, 1 << 25, 8, 24, 1, ONE + 40), (4, 0, 1 << 25, 4, 12, 1, ONE)])
+def test_store_shapes(rules, rows, f64, n, value, reads, lines, shape):
+    assert rules.rule_store(rows, f64, n, value, reads, lines) == shape
