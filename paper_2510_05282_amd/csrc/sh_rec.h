@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include "sh_core.h"
+#include "sh_fwd.h"
 #include "sh_rec_constants.h"
 
 namespace shk {
@@ -16,7 +17,6 @@ namespace shk {
 // Yb_{m-1} = 0 and Yb_{m-2} = -1 make it d_m = d_m (z 0 - 1 (-1)).  Rows are padded so
 // that a block of up to 8 pairs from any l <= kRecLmax stays inside: a wave reads a
 // block's pairs in one or two scalar loads.
-constexpr int kRecUnroll = 4;
 constexpr int kRecRow = (shc::kRecLmax + 1 + 8 + 7) / 8 * 8;
 template <typename S>
 struct alignas(64) RecTable {
@@ -36,12 +36,13 @@ template <typename S> constexpr RecTable<S> kRecTable{};
 // m > 0 the value of +m comes just before that of -m.  keep
 // masks the m = 0 rows of l > 0 at the origin, as in eval_unit.  T is double, float
 // or a clang vector of them (that many points at once).  The loops run over the
-// runtime lmax, kRecUnroll degrees at a time, and over m = part, part + parts, ... only:
+// runtime lmax, UNROLL degrees at a time (8 at most), and over m = part, part + parts, ... only:
 // the values do not depend on how many parts a point is dealt to.
-template <typename T, typename Store>
+template <typename T, int UNROLL = 4, typename Store>
 __host__ __device__ __forceinline__ void eval_unit_rec(T x, T y, T z, T keep, int lmax, Store&& store, int part = 0,
                                                        int parts = 1)
 {
+    static_assert(UNROLL <= 8, "the table's rows are padded for 8");
     using S = scalar_t<T>;
     T c = T(S(1)), s = T(S(0));  // C_m + i S_m = (x + i y)^m
     auto step = [&] {
@@ -62,12 +63,12 @@ __host__ __device__ __forceinline__ void eval_unit_rec(T x, T y, T z, T keep, in
         };
         T y2 = T(S(0)), y1 = T(row_m[0][0]);  // Yb_{l-2}^m, Yb_{l-1}^m
         put(m, y1);
-        for (int l0 = m + 1; l0 <= lmax; l0 += kRecUnroll) {
-            S a[kRecUnroll], b[kRecUnroll];
+        for (int l0 = m + 1; l0 <= lmax; l0 += UNROLL) {
+            S a[UNROLL], b[UNROLL];
 #pragma unroll
-            for (int i = 0; i < kRecUnroll; ++i) a[i] = row_m[l0 - m + i][0], b[i] = row_m[l0 - m + i][1];
+            for (int i = 0; i < UNROLL; ++i) a[i] = row_m[l0 - m + i][0], b[i] = row_m[l0 - m + i][1];
 #pragma unroll
-            for (int i = 0; i < kRecUnroll; ++i) {
+            for (int i = 0; i < UNROLL; ++i) {
                 if (l0 + i > lmax) break;
                 const T yl = a[i] * (z * y1 - b[i] * y2);
                 y2 = y1;
@@ -185,13 +186,13 @@ __host__ __device__ __forceinline__ void grad_unit_rec(T x, T y, T z, int lmax, 
 // complex_unit does for the explicit ones: Y_l^0 = R_l^0, and for m > 0
 //     Y_l^m = (-1)^m (R_l^m + i R_l^-m) / sqrt(2),   Y_l^-m = (R_l^m - i R_l^-m) / sqrt(2);
 // sink(l, m, re, im).
-template <typename T, typename Sink>
+template <typename T, int UNROLL = 4, typename Sink>
 __host__ __device__ __forceinline__ void complex_unit_rec(T x, T y, T z, T keep, int lmax, Sink&& sink)
 {
     using S = scalar_t<T>;
     const T h = T(S(0.70710678118654752440));  // 1/sqrt(2)
     T cos_part = T(S(0));
-    eval_unit_rec<T>(x, y, z, keep, lmax, [&](int l, int m, T v) {
+    eval_unit_rec<T, UNROLL>(x, y, z, keep, lmax, [&](int l, int m, T v) {
         if (m == 0) {
             sink(l, 0, v, T(S(0)));
         } else if (m > 0) {
@@ -207,12 +208,71 @@ __host__ __device__ __forceinline__ void complex_unit_rec(T x, T y, T z, T keep,
 
 // Spinor harmonics (eq. spinorial) from complex_unit_rec, with the coefficient
 // table of sh_rec_constants.h; sink(k, c, re, im) as for spinor_unit.
-template <typename T, typename Sink>
+template <typename T, int UNROLL = 4, typename Sink>
 __host__ __device__ __forceinline__ void spinor_unit_rec(T x, T y, T z, T keep, int lmax, Sink&& sink)
 {
-    complex_unit_rec<T>(x, y, z, keep, lmax, [&](int l, int m, T re, T im) {
+    complex_unit_rec<T, UNROLL>(x, y, z, keep, lmax, [&](int l, int m, T re, T im) {
         spinor_spread(l, m, re, im, [](int ll, int q) { return shc::kSpinP[ll][q]; }, sink);
     });
+}
+
+// How a forward launch by recurrence is shaped.
+struct RecShape {
+    bool wide;   // 16 bytes of adjacent points per lane and row, else one point
+    bool split;  // the m of a point dealt to four waves
+    int unroll;  // degrees at a time: 1, 4 or 8
+    size_t lds;  // reserved
+};
+constexpr int64_t kRecSplitPoints = int64_t(1) << 16, kRecCapPoints = int64_t(1) << 19;
+constexpr int64_t kRecThrottleBytes = int64_t(23) << 24;
+inline size_t rec_lds(int64_t n, bool lines) { return !lines && n >= kRecCapPoints ? kCapLds1 : kCapLds2; }
+
+// Real harmonics of n points, `bytes` written (us, points per lane / KiB of LDS reserved):
+//   below 2^16 points  the m dealt to four waves, whatever is written: such a launch is one chain
+//                      of work long: 10001 points, lmax 16 FP64 26.9 -> 8.6, FP32 25.3 -> 7.4; 60000,
+//                      lmax 16 FP64 27.9 against 2/54 35.6, 30000, lmax 24 30.2 / 62.5, FP32 60000 32.3
+//                      / 64.2
+//   then one point     FP64 up to 5 x 2^14 points, FP32 to 2^17 (where several leave CUs idle):
+//                      lmax 20, 65537 44.6 / 2/54 49.7, FP32 lmax 24, 100000 51.2 / 4/54 65.1; and
+//                      below 2^27 bytes, FP32 from 3 x 2^16 points below 3 x 2^25: lmax 10, 262144 26.7 /
+//                      4/54 23.0, 170001 16.8 / 19.5, lmax 12, 170001 22.0 / 23.6
+//   wide               200001 points, lmax 16 FP64 2/54 88, 2/84 114 (one workgroup per CU
+//                      leaves a short last round); FP32 4/54 47; 4000000 FP64 2/54 1730,
+//                      2/84 1761; off the lines from 2^19 points 2/84: 1000001 points, lmax 16 FP64 485,
+//                      2/54 500, 1/0 598; FP32, 2000001 4/84 473, 4/54 515
+//   FP64, 23 x 2^24    resident all at once, the waves meet in the write path: four degrees at a
+//   bytes and more     time are slower than one.  Up to 33 x 2^12 points eight with one point per lane:
+//                      lmax 24, 106001 2/54 x 4 144, 1/0 x 8 110, lmax 20, 131072 104 / 84; to 3 x 2^16 one
+//                      with two: lmax 20, 163840 119 / 112, 188001 127 / 121; then four: 204801 132, one 146
+template <typename TIO>
+inline RecShape rec_shape(int64_t n, int64_t bytes, bool lines)
+{
+    constexpr bool f64 = sizeof(TIO) == 8;
+    if (n < kRecSplitPoints) return {false, true, 4, 0};
+    if (f64 && bytes >= kRecThrottleBytes && n <= int64_t(3) << 16)
+        return n < int64_t(33) << 12 ? RecShape{false, false, 8, 0} : RecShape{true, false, 1, kCapLds2};
+    const bool wide = f64 ? n > int64_t(5) << 14 && bytes >= kWideBytes
+                          : (n > int64_t(1) << 17 && bytes >= kWideBytes) ||
+                                (n >= int64_t(3) << 16 && bytes >= 3 * (kWideBytes >> 2));
+    return wide ? RecShape{true, false, 4, rec_lds(n, lines)} : RecShape{false, false, 4, 0};
+}
+
+// Complex and spinor harmonics.  FP32 takes several points from 2^16 on, where the CUs no longer
+// hold one per lane in one round (spinor lmax 16, 14514 points 90.6 against 102; complex lmax 24, 30000
+// 58.4 / 67.5; lmax 20, 80001 66.5 / 55.7).  FP64 (one point, 16 bytes) unrolls as the real harmonics:
+// complex lmax 24, 57001 points x 4 154, x 8 120, 90001 x 4 175, x 1 162, 106001 x 4 201, x 1 216; spinor
+// lmax 24, 30001 x 4 302, x 8 285, lmax 16, 65537 x 4 247, x 8 272.
+template <typename TIO, bool SPINOR>
+inline RecShape rec_cplx_shape(int64_t n, int64_t bytes, bool lines)
+{
+    if (bytes < kWideBytes) return {false, false, 4, 0};
+    if (sizeof(TIO) == 4 && n <= kRecSplitPoints) return {false, false, 4, 0};
+    int unroll = 4;
+    if (sizeof(TIO) == 8 && bytes >= kRecThrottleBytes) {
+        if (n <= (SPINOR ? kRecSplitPoints : int64_t(5) << 14)) unroll = 8;
+        else if (!SPINOR && n <= int64_t(3) << 15) unroll = 1;
+    }
+    return {true, false, unroll, rec_lds(n, lines)};
 }
 
 }  // namespace shk

@@ -36,7 +36,7 @@ constexpr int64_t kRecChunk = int64_t(1) << 28;
 // TIO = double: up to 2 points per lane (PPL = 2); float: 4 (PPL = 4); both then store
 // 16 bytes per lane and row.  Points are normalised in FP64 either way.  SPLIT: the
 // workgroup takes 64 lanes' worth of points and deals their m to its four waves.
-template <typename TIO, int PPL, bool SPLIT>
+template <typename TIO, int PPL, bool SPLIT, int UNROLL>
 __global__ __launch_bounds__(kRecBlock) void rec_kernel(const TIO* __restrict__ xyz, TIO* __restrict__ out,
                                                         uint32_t n, int64_t ld, int lmax)
 {
@@ -52,47 +52,36 @@ __global__ __launch_bounds__(kRecBlock) void rec_kernel(const TIO* __restrict__ 
     auto store = [&](int l, int m, V v) {
         *reinterpret_cast<U*>(reinterpret_cast<char*>(out + int64_t(row(l, m)) * ld) + boff) = v;
     };
-    if constexpr (SPLIT)
-        eval_unit_rec<V>(x, y, z, k, lmax, store, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kRecBlock / 64);
-    else
-        eval_unit_rec<V>(x, y, z, k, lmax, store);
+    const int part = SPLIT ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    eval_unit_rec<V, UNROLL>(x, y, z, k, lmax, store, part, SPLIT ? kRecBlock / 64 : 1);
 }
 
-template <typename TIO, int PPL, bool SPLIT>
+template <typename TIO, int PPL, bool SPLIT, int UNROLL>
 static hipError_t launch_rec_one(int lmax, int64_t n, const TIO* xyz, TIO* out, int64_t ld, hipStream_t s, size_t lds)
 {
     constexpr int kLanes = SPLIT ? 64 : kRecBlock;
     const unsigned grid = unsigned(((n + PPL - 1) / PPL + kLanes - 1) / kLanes);
-    hipLaunchKernelGGL((rec_kernel<TIO, PPL, SPLIT>), dim3(grid), dim3(kRecBlock), lds, s, xyz, out, uint32_t(n), ld,
-                       lmax);
+    hipLaunchKernelGGL((rec_kernel<TIO, PPL, SPLIT, UNROLL>), dim3(grid), dim3(kRecBlock), lds, s, xyz, out,
+                       uint32_t(n), ld, lmax);
     return hipGetLastError();
 }
-
-// How the forward launches are shaped (us, points per lane / KiB of LDS reserved; a
-// launch that writes less than kWideBytes takes one point per lane, as store_shape):
-//   below 2^16 points  the m dealt to four waves: such a launch is one chain of work long:
-//                      10001 points, lmax 16 FP64 26.9 -> 8.6, FP32 25.3 -> 7.4 (12 MB)
-//   wide, 2^19 points  off the lines (see store_shape): 1000001 points, lmax 16 FP64 2/84
-//                      485, 2/54 500, 1/0 598; FP32, 2000001 4/84 473, 4/54 515
-//   wide otherwise     200001 points, lmax 16 FP64 2/54 88, 2/84 114 (one workgroup per CU
-//                      leaves a short last round); FP32 4/54 47; 4000000 FP64 2/54 1730,
-//                      2/84 1761
-constexpr int64_t kRecSplitPoints = int64_t(1) << 16, kRecCapPoints = int64_t(1) << 19;
-inline size_t rec_lds(int64_t n, bool lines) { return !lines && n >= kRecCapPoints ? kCapLds1 : kCapLds2; }
 
 template <typename TIO>
 hipError_t launch_rec(int lmax, int64_t n, const TIO* xyz, TIO* out, int64_t ld, hipStream_t s)
 {
     constexpr int kVec = 16 / sizeof(TIO);
-    const int64_t bytes = n * nfun(lmax) * int64_t(sizeof(TIO));
-    const bool wide = bytes >= kWideBytes;
-    const size_t lds = wide ? rec_lds(n, on_lines(out, ld * sizeof(TIO))) : 0;
+    const RecShape f = rec_shape<TIO>(n, n * nfun(lmax) * int64_t(sizeof(TIO)), on_lines(out, ld * sizeof(TIO)));
     for (int64_t c0 = 0; c0 < n; c0 += kRecChunk) {
         const int64_t nc = n - c0 < kRecChunk ? n - c0 : kRecChunk;
         const TIO* x = xyz + 3 * c0;
-        const hipError_t e = wide && nc >= kVec   ? launch_rec_one<TIO, kVec, false>(lmax, nc, x, out + c0, ld, s, lds)
-                             : n < kRecSplitPoints ? launch_rec_one<TIO, 1, true>(lmax, nc, x, out + c0, ld, s, 0)
-                                                   : launch_rec_one<TIO, 1, false>(lmax, nc, x, out + c0, ld, s, 0);
+        TIO* o = out + c0;
+        const hipError_t e =
+            f.split                  ? launch_rec_one<TIO, 1, true, 4>(lmax, nc, x, o, ld, s, f.lds)
+            : !f.wide || nc < kVec
+                ? (f.unroll == 8 ? launch_rec_one<TIO, 1, false, 8>(lmax, nc, x, o, ld, s, f.lds)
+                                 : launch_rec_one<TIO, 1, false, 4>(lmax, nc, x, o, ld, s, f.lds))
+            : f.unroll == 1          ? launch_rec_one<TIO, kVec, false, 1>(lmax, nc, x, o, ld, s, f.lds)
+                                     : launch_rec_one<TIO, kVec, false, 4>(lmax, nc, x, o, ld, s, f.lds);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -236,7 +225,7 @@ template hipError_t launch_grad_rec<float>(int, int64_t, const float*, const flo
 
 // Complex (SPINOR = false) or spinor harmonics by recurrence, any input interface:
 // the lanes and layout of fwd_complex_kernel / fwd_spinor_kernel, lmax at run time.
-template <typename TIO, int PPL, bool SPINOR>
+template <typename TIO, int PPL, bool SPINOR, int UNROLL>
 __global__ __launch_bounds__(kRecBlock) void rec_cplx_kernel(const TIO* __restrict__ in0, TIO* __restrict__ out,
                                                              uint32_t n, int64_t ld, const TIO* __restrict__ in1,
                                                              In mode, int lmax)
@@ -253,17 +242,17 @@ __global__ __launch_bounds__(kRecBlock) void rec_cplx_kernel(const TIO* __restri
         *reinterpret_cast<W*>(reinterpret_cast<char*>(out + 2 * r * ld) + boff) = interleave<TIO, PPL>(re, im);
     };
     if constexpr (SPINOR)
-        spinor_unit_rec<V>(x, y, z, k, lmax, [&](int s, int c, V re, V im) { put(2 * s + c, re, im); });
+        spinor_unit_rec<V, UNROLL>(x, y, z, k, lmax, [&](int s, int c, V re, V im) { put(2 * s + c, re, im); });
     else
-        complex_unit_rec<V>(x, y, z, k, lmax, [&](int l, int m, V re, V im) { put(row(l, m), re, im); });
+        complex_unit_rec<V, UNROLL>(x, y, z, k, lmax, [&](int l, int m, V re, V im) { put(row(l, m), re, im); });
 }
 
-template <typename TIO, int PPL, bool SPINOR>
+template <typename TIO, int PPL, bool SPINOR, int UNROLL>
 static hipError_t launch_rec_cplx_one(int lmax, int64_t n, In mode, const TIO* a, const TIO* b, TIO* out,
                                       int64_t ld, hipStream_t s, size_t lds)
 {
     const unsigned grid = unsigned(((n + PPL - 1) / PPL + kRecBlock - 1) / kRecBlock);
-    hipLaunchKernelGGL((rec_cplx_kernel<TIO, PPL, SPINOR>), dim3(grid), dim3(kRecBlock), lds, s, a, out,
+    hipLaunchKernelGGL((rec_cplx_kernel<TIO, PPL, SPINOR, UNROLL>), dim3(grid), dim3(kRecBlock), lds, s, a, out,
                        uint32_t(n), ld, b, mode, lmax);
     return hipGetLastError();
 }
@@ -276,15 +265,20 @@ static hipError_t launch_rec_cplx(int lmax, int64_t n, int input, const TIO* in0
     constexpr int64_t kValue = 2 * sizeof(TIO);
     const In mode = In(input);
     const int64_t stride = mode == In::kAngles ? 1 : 3;
-    const bool wide = n * nfun(lmax) * (SPINOR ? 4 : 1) * kValue >= kWideBytes;
-    const size_t lds = wide ? rec_lds(n, on_lines(out, ld * kValue)) : 0;
+    const RecShape f = rec_cplx_shape<TIO, SPINOR>(n, n * nfun(lmax) * (SPINOR ? 4 : 1) * kValue,
+                                                   on_lines(out, ld * kValue));
     for (int64_t c0 = 0; c0 < n; c0 += kRecChunk) {
         const int64_t nc = n - c0 < kRecChunk ? n - c0 : kRecChunk;
         const TIO *a = in0 + stride * c0, *b = mode == In::kAngles ? in1 + c0 : in1;
-        const hipError_t e =
-            wide && nc >= kVec
-                ? launch_rec_cplx_one<TIO, kVec, SPINOR>(lmax, nc, mode, a, b, out + 2 * c0, ld, s, lds)
-                : launch_rec_cplx_one<TIO, 1, SPINOR>(lmax, nc, mode, a, b, out + 2 * c0, ld, s, lds);
+        TIO* o = out + 2 * c0;
+        hipError_t e = hipErrorInvalidValue;
+        if (kVec > 1 && (!f.wide || nc < kVec))
+            e = launch_rec_cplx_one<TIO, 1, SPINOR, 4>(lmax, nc, mode, a, b, o, ld, s, f.lds);
+        else if (f.unroll == 4)
+            e = launch_rec_cplx_one<TIO, kVec, SPINOR, 4>(lmax, nc, mode, a, b, o, ld, s, f.lds);
+        else if constexpr (sizeof(TIO) == 8)  // the others are FP64's
+            e = f.unroll == 8 || SPINOR ? launch_rec_cplx_one<TIO, 1, SPINOR, 8>(lmax, nc, mode, a, b, o, ld, s, f.lds)
+                                        : launch_rec_cplx_one<TIO, 1, SPINOR, 1>(lmax, nc, mode, a, b, o, ld, s, f.lds);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

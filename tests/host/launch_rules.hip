@@ -1,6 +1,7 @@
 // Test-only: host build of the rules that choose a launch from sizes and alignment, so that
 // the lines between launches can be checked on the CPU.
 #include "../../paper_2510_05282_amd/csrc/sh_proj.h"
+#include "../../paper_2510_05282_amd/csrc/sh_rec.h"
 
 // 0: no tables in LDS; else how many workgroups go side by side.
 template <typename TIO, int LMAX>
@@ -54,4 +55,25 @@ extern "C" int rule_store(int rows, int f64, long n, int value, int in_bytes, in
     case 400: return store<400>(f64, n, value, in_bytes, lines);
     default: return -1;
     }
+}
+
+// KiB of LDS reserved, plus 1000 where lanes take several points, 2000 where the m are split,
+// and 10000 times the degrees at a time.  kind: 0 real, 1 complex, 2 spinor.
+static int rec(const shk::RecShape& f)
+{
+    return 10000 * f.unroll + (f.wide ? 1000 : 0) + (f.split ? 2000 : 0) + int(f.lds / 1024);
+}
+
+template <typename TIO>
+static int rec_of(int kind, int lmax, int64_t n, int lines)
+{
+    const int64_t b = n * (lmax + 1) * (lmax + 1) * int64_t(sizeof(TIO));
+    if (kind == 0) return rec(shk::rec_shape<TIO>(n, b, lines));
+    return kind == 1 ? rec(shk::rec_cplx_shape<TIO, false>(n, 2 * b, lines))
+                     : rec(shk::rec_cplx_shape<TIO, true>(n, 8 * b, lines));
+}
+
+extern "C" int rule_rec(int kind, int f64, int lmax, long n, int lines)
+{
+    return f64 ? rec_of<double>(kind, lmax, n, lines) : rec_of<float>(kind, lmax, n, lines);
 }

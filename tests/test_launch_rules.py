@@ -24,6 +24,7 @@ def rules(tmp_path_factory):
                           stderr=subprocess.DEVNULL)
     L = ctypes.CDLL(so)
     L.rule_store.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int, ctypes.c_int, ctypes.c_int]
+    L.rule_rec.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int]
     L.rule_proj_lds.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int, ctypes.c_int]
     return L
 
@@ -77,3 +78,30 @@ ONE, WIDE = 0, 1000  # points per lane; plus the KiB reserved
     (4, 1, 1 << 25, 8, 24, 1, ONE + 40), (4, 0, 1 << 25, 4, 12, 1, ONE)])
 def test_store_shapes(rules, rows, f64, n, value, reads, lines, shape):
     assert rules.rule_store(rows, f64, n, value, reads, lines) == shape
+
+
+REAL, COMPLEX, SPINOR = 0, 1, 2
+SPLIT = 2000
+
+
+@pytest.mark.parametrize("kind,f64,lmax,n,lines,unroll,shape", [
+    # split below 2^16 points, whatever is written
+    (REAL, 1, 16, 60000, 1, 4, SPLIT), (REAL, 1, 24, 30000, 1, 4, SPLIT), (REAL, 0, 24, 65535, 0, 4, SPLIT),
+    (REAL, 1, 10, 10001, 0, 4, SPLIT),
+    # one point per lane while several would leave CUs idle
+    (REAL, 1, 16, 65537, 0, 4, ONE), (REAL, 1, 16, 80000, 1, 4, ONE), (REAL, 1, 16, 100000, 1, 4, WIDE + 54),
+    (REAL, 0, 24, 100000, 1, 4, ONE), (REAL, 0, 16, 131072, 1, 4, ONE), (REAL, 0, 20, 140001, 0, 4, WIDE + 54),
+    (REAL, 0, 10, 262144, 1, 4, WIDE + 54), (REAL, 0, 12, 170001, 0, 4, ONE), (REAL, 1, 10, 120000, 1, 4, ONE),
+    (REAL, 1, 16, 1_000_001, 0, 4, WIDE + 84), (REAL, 1, 16, 1_000_000, 1, 4, WIDE + 54),
+    # FP64 from 23 x 2^24 bytes on
+    (REAL, 1, 24, 106_001, 0, 8, ONE), (REAL, 1, 20, 131_072, 1, 8, ONE), (REAL, 1, 20, 106_001, 0, 4, WIDE + 54),
+    (REAL, 1, 20, 163_840, 1, 1, WIDE + 54), (REAL, 1, 24, 188_001, 0, 1, WIDE + 54),
+    (REAL, 1, 24, 204_801, 0, 4, WIDE + 54), (COMPLEX, 1, 20, 57001, 0, 8, WIDE + 54),
+    (COMPLEX, 1, 24, 57001, 0, 8, WIDE + 54), (COMPLEX, 1, 24, 90001, 0, 1, WIDE + 54),
+    (COMPLEX, 1, 24, 106_001, 0, 4, WIDE + 54), (COMPLEX, 1, 16, 80001, 0, 4, WIDE + 54),
+    (SPINOR, 1, 24, 30001, 0, 8, WIDE + 54), (SPINOR, 1, 16, 65537, 0, 4, WIDE + 54),
+    # FP32 complex and spinor: one point while the CUs hold that in one round
+    (SPINOR, 0, 16, 14514, 1, 4, ONE), (SPINOR, 0, 24, 6711, 0, 4, ONE), (SPINOR, 0, 9, 65536, 1, 4, ONE),
+    (COMPLEX, 0, 24, 30000, 1, 4, ONE), (COMPLEX, 0, 20, 80001, 0, 4, WIDE + 54), (COMPLEX, 0, 9, 131_073, 0, 4, ONE)])
+def test_recurrence_shapes(rules, kind, f64, lmax, n, lines, unroll, shape):
+    assert rules.rule_rec(kind, f64, lmax, n, lines) == 10000 * unroll + shape

@@ -91,3 +91,38 @@ def test_spinors_of_angles_and_unit_vectors(dev, dtype, lmax, more):
     u = torch.nn.functional.normalize(_points(n, torch.float64, dev), dim=1).to(dtype).contiguous()
     _agree(lambda v: torch.view_as_real(sh.sh_eval_spinor_unit(lmax, v).reshape(-1, v.shape[0])).movedim(1, -1), u, n,
            per_point)
+
+
+@pytest.mark.parametrize("dtype,lmax,n", [
+    (torch.float64, 16, 65537), (torch.float64, 17, 100003), (torch.float64, 24, 65536), (torch.float64, 24, 98305),
+    (torch.float64, 24, 135167), (torch.float64, 24, 135169), (torch.float64, 22, 196609), (torch.float32, 24, 131072),
+    (torch.float32, 24, 131073), (torch.float32, 19, 140003), (torch.float32, 10, 262146)])
+def test_recurrence_against_the_split_launch(dev, orc, dtype, lmax, n):
+    """The pieces are below 2^16 points, where the m are dealt to four waves whatever is written."""
+    print("case: recurrence, lmax", lmax, "n", n, dtype, flush=True)
+    x = _points(n, dtype, dev)
+    fn = sh.sh_eval_rec if dtype == torch.float64 else sh.sh_eval_rec_f32
+    y = fn(lmax, x)
+    for i in range(0, n, 30001):
+        assert torch.equal(y[:, i:i + 30001], fn(lmax, x[i:i + 30001].contiguous()))
+    tail = slice(n - 35, n)
+    ref = orc.eval_xyz(lmax, x[tail].double().cpu().numpy())
+    tol = 1e-12 if dtype == torch.float64 else max(5e-6, 1e-6 * (lmax + 1))
+    assert np.abs(y[:, tail].cpu().numpy().astype(np.longdouble) - ref).max() <= tol
+
+
+@pytest.mark.parametrize("kind,dtype,lmax,n", [
+    ("complex", torch.float64, 24, 50001), ("complex", torch.float64, 24, 81921), ("complex", torch.float64, 20, 98305),
+    ("complex", torch.float32, 18, 65537), ("complex", torch.float32, 18, 65538), ("spinor", torch.float64, 24, 20001),
+    ("spinor", torch.float32, 16, 65536), ("spinor", torch.float32, 16, 65537), ("spinor", torch.float32, 11, 70003)])
+def test_complex_recurrence(dev, kind, dtype, lmax, n):
+    """Pieces small enough for one point per lane, four degrees at a time."""
+    print("case: recurrence,", kind, "lmax", lmax, "n", n, dtype, flush=True)
+    per_point = (lmax + 1) ** 2 * (torch.finfo(dtype).bits // 8) * (2 if kind == "complex" else 8)
+    f = sh.sh_eval_complex_rec if kind == "complex" else sh.sh_eval_spinor_rec
+    x = _points(n, dtype, dev)
+    y = f(lmax, x)
+    m = (WIDE - 1) // per_point
+    for i in range(0, n, m):
+        p = f(lmax, x[i:i + m].contiguous())
+        assert torch.equal(torch.view_as_real(y[..., i:i + m].contiguous()), torch.view_as_real(p))
