@@ -127,7 +127,8 @@ __host__ __device__ __forceinline__ void grad_unit_rec_part(T x, T y, T z, int l
                 const int l = l0 + i <= lmax ? l0 + i : lmax;
                 a[i] = row_m[l0 - m + i][0], b[i] = row_m[l0 - m + i][1];
                 gc[i] = g(row(l, m));
-                gs[i] = g(row(l, -m));
+                // m = 0 has no sine rows: read as more of the cosine's, or not at all
+                gs[i] = std::is_arithmetic_v<T> && UNROLL == 1 && m == 0 ? zero : g(row(l, -m));
             }
 #ifdef __HIP_DEVICE_COMPILE__
             __builtin_amdgcn_sched_barrier(0);  // the reads stay ahead of the arithmetic
@@ -273,6 +274,40 @@ inline RecShape rec_cplx_shape(int64_t n, int64_t bytes, bool lines)
         else if (!SPINOR && n <= int64_t(3) << 15) unroll = 1;
     }
     return {true, false, unroll, rec_lds(n, lines)};
+}
+
+// How a backward launch by recurrence is shaped.
+struct GradRecShape {
+    int ppl;     // adjacent points per lane
+    bool split;  // the m of a point dealt to four waves
+    int unroll;  // degrees whose reads are issued together
+};
+constexpr int64_t kGradRecNarrow = int64_t(1) << 16;
+
+// Bound by the reads of G (us, SPLIT or whole, points per lane x degrees):
+//   below 2^16 points  10001, lmax 16: FP64 split 1 x 8 11.0, 1 x 2 16.6, 2 x 2 18.9; FP32 10.1, 15.0, 17.7
+//   then, split 2 x 2  lmax 16, 130001 FP64 50.9 / whole 1 x 2 69; FP32 24.6 / 40.7; 800001 FP32 178 / whole
+//                      4 x 2 204
+//   FP64 from 2^18     lmax 16, 400001 whole 2 x 1 153, 1 x 1 155, 2 x 2 170-175, 1 x 2 182; 2000001, lmax 10 340 /
+//                      347 / 364 / 405 (held to 128 registers, four waves a SIMD; 238 against 208 at 130
+//                      registers); up to 5 x 2^16, where all lanes are resident with one point each, whole 1 x 2:
+//                      lmax 9, 270001 42.0, 2 x 1 44.5.  Few rows, 1 x 1: lmax 1, 4000001 54.5, 2 x 1 69,
+//                      2 x 2 67-75, lmax 4 174 / 180 / 192, lmax 7, 400001 37.5 / 38.9 / 43
+//   FP32 from 2^20     lmax 16, 2000001 whole 4 x 2 389, 2 x 2 433, 1 x 2 463.  Up to lmax 3 from 2^19 whole
+//                      1 x 2: lmax 1, 1000001 9.2 / split 12.5, 4000001 27.5 / 4 x 2 32.9; lmax 4, 4000001
+//                      102 / 101
+template <typename TIO>
+inline GradRecShape grad_rec_shape(int lmax, int64_t n)
+{
+    if (n < kGradRecNarrow) return {1, true, 8};
+    if constexpr (sizeof(TIO) == 8) {
+        if (n < int64_t(1) << 18) return {2, true, 2};
+        if (lmax < 8) return {1, false, 1};
+        return n < int64_t(5) << 16 ? GradRecShape{1, false, 2} : GradRecShape{2, false, 1};
+    } else {
+        if (n < int64_t(1) << (lmax < 4 ? 19 : 20)) return {2, true, 2};
+        return lmax < 4 ? GradRecShape{1, false, 2} : GradRecShape{4, false, 2};
+    }
 }
 
 }  // namespace shk

@@ -102,19 +102,10 @@ template hipError_t launch_rec<float>(int, int64_t, const float*, float*, int64_
 // Bound by the reads of G, and by their latency wherever few waves have few reads under
 // way: with every read waited for before the next and no split, 200001 points at lmax 16
 // took 124 us in FP64 (3.8 TB/s) and 110 in FP32 (2.1), 10001 points 84 and 75; now 81
-// (5.8 TB/s), 47 (5.0), 11 and 10.
-// Which one, in us as SPLIT or not, points per lane, reads unrolled by (lmax 16):
-//   below 2^16 points  10001: FP64 split 1 x 8 11.0, 1 x 2 16.6, 2 x 2 18.9; FP32 10.1, 15.0, 17.7
-//   then, split 2 x 2  200001: FP64 split 2 x 2 81, whole 2 x 2 79-85, whole 1 x 1 107; FP32
-//                      split 47, whole 4 x 2 69; 800001: FP32 split 178, whole 4 x 2 204
-//   from 2^18 (FP64)   520001: whole 2 x 2 208 (held to 128 registers, four waves a SIMD;
-//                      238 at 130), split 272; 2000001: whole 831, split 858
-//   from 2^20 (FP32)   2000001: whole 4 x 2 393, whole 2 x 2 433, split 447
-constexpr int64_t kGradRecNarrow = int64_t(1) << 16;
-template <typename TIO> constexpr int64_t kGradRecSplit = int64_t(1) << (sizeof(TIO) == 8 ? 18 : 20);
-
+// (5.8 TB/s), 47 (5.0), 11 and 10.  grad_rec_shape says which launch.  FP32's split launches are
+// held to 72 registers, seven waves a SIMD: 400001 points at lmax 9 26.3 us, 28.6 at six waves.
 template <typename TIO, int PPL, bool SPLIT, int UNROLL, bool NT>
-__global__ __launch_bounds__(kRecBlock, !SPLIT && sizeof(TIO) == 8 ? 4 : 1) void grad_rec_kernel(
+__global__ __launch_bounds__(kRecBlock, !SPLIT && sizeof(TIO) == 8 ? 4 : SPLIT && sizeof(TIO) == 4 ? 7 : 1) void grad_rec_kernel(
     const TIO* __restrict__ xyz, const TIO* __restrict__ G, TIO* __restrict__ gxyz, uint32_t n, int64_t ldg, int lmax)
 {
     using V = typename vec_of<TIO, PPL>::type;
@@ -156,26 +147,18 @@ __global__ __launch_bounds__(kRecBlock, !SPLIT && sizeof(TIO) == 8 ? 4 : 1) void
         grad_unit_rec<V, UNROLL>(x, y, z, lmax, g_at, v[0], v[1], v[2]);
     }
     // gxyz may be xyz: a last lane that read its neighbour's points too, which may be
-    // gradients by then, stores only its own
+    // gradients by then, stores only its own (only there is i0 no multiple of PPL)
     TIO* o = gxyz + 3 * size_t(i0);
-    const int first = PPL > 1 ? int(t * PPL - i0) : 0;
-    TIO r[3 * PPL];
+    const int first = int(-i0 % PPL);
 #pragma unroll
     for (int q = 0; q < PPL; ++q) {
+        if (q < PPL - 1 && q < first) continue;
         const double gx = double(lane<V, PPL>(v[0], q)), gy = double(lane<V, PPL>(v[1], q)),
                      gz = double(lane<V, PPL>(v[2], q));
         const double uv = xb[q] * gx + yb[q] * gy + zb[q] * gz;
-        r[3 * q + 0] = TIO(rinv[q] * (gx - xb[q] * uv));
-        r[3 * q + 1] = TIO(rinv[q] * (gy - yb[q] * uv));
-        r[3 * q + 2] = TIO(rinv[q] * (gz - zb[q] * uv));
-    }
-    if (first == 0) {
-#pragma unroll
-        for (int k = 0; k < 3 * PPL; ++k) o[k] = r[k];
-    } else {
-#pragma unroll
-        for (int k = 0; k < 3 * PPL; ++k)
-            if (k >= 3 * first) o[k] = r[k];
+        o[3 * q + 0] = TIO(rinv[q] * (gx - xb[q] * uv));
+        o[3 * q + 1] = TIO(rinv[q] * (gy - yb[q] * uv));
+        o[3 * q + 2] = TIO(rinv[q] * (gz - zb[q] * uv));
     }
 }
 
@@ -195,14 +178,18 @@ static hipError_t launch_grad_rec_nt(int lmax, int64_t n, const TIO* xyz, const 
                                      hipStream_t s)
 {
     constexpr int kVec = 16 / sizeof(TIO);
+    const GradRecShape f = grad_rec_shape<TIO>(lmax, n);
     for (int64_t c0 = 0; c0 < n; c0 += kRecChunk) {
         const int64_t nc = n - c0 < kRecChunk ? n - c0 : kRecChunk;
         const TIO *x = xyz + 3 * c0, *g = G + c0;
         TIO* o = gxyz + 3 * c0;
-        const hipError_t e =
-            n < kGradRecNarrow || nc < kVec ? launch_grad_rec_one<TIO, 1, true, 8, NT>(lmax, nc, x, g, ldg, o, s)
-            : n < kGradRecSplit<TIO>        ? launch_grad_rec_one<TIO, 2, true, 2, NT>(lmax, nc, x, g, ldg, o, s)
-                                            : launch_grad_rec_one<TIO, kVec, false, 2, NT>(lmax, nc, x, g, ldg, o, s);
+        hipError_t e;
+        if (f.unroll == 8 || nc < kVec) e = launch_grad_rec_one<TIO, 1, true, 8, NT>(lmax, nc, x, g, ldg, o, s);
+        else if (f.split) e = launch_grad_rec_one<TIO, 2, true, 2, NT>(lmax, nc, x, g, ldg, o, s);
+        else if (f.ppl == 1 && f.unroll == 2) e = launch_grad_rec_one<TIO, 1, false, 2, NT>(lmax, nc, x, g, ldg, o, s);
+        else if constexpr (kVec == 4) e = launch_grad_rec_one<TIO, 4, false, 2, NT>(lmax, nc, x, g, ldg, o, s);
+        else if (f.ppl == 1) e = launch_grad_rec_one<TIO, 1, false, 1, NT>(lmax, nc, x, g, ldg, o, s);
+        else e = launch_grad_rec_one<TIO, 2, false, 1, NT>(lmax, nc, x, g, ldg, o, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

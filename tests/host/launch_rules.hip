@@ -73,6 +73,13 @@ static int rec_of(int kind, int lmax, int64_t n, int lines)
                      : rec(shk::rec_cplx_shape<TIO, true>(n, 8 * b, lines));
 }
 
+// Points per lane, plus 2000 where the m are split, and 10000 times the degrees at a time.
+extern "C" int rule_grad_rec(int f64, int lmax, long n)
+{
+    const shk::GradRecShape f = f64 ? shk::grad_rec_shape<double>(lmax, n) : shk::grad_rec_shape<float>(lmax, n);
+    return 10000 * f.unroll + (f.split ? 2000 : 0) + f.ppl;
+}
+
 extern "C" int rule_rec(int kind, int f64, int lmax, long n, int lines)
 {
     return f64 ? rec_of<double>(kind, lmax, n, lines) : rec_of<float>(kind, lmax, n, lines);

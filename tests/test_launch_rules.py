@@ -25,6 +25,7 @@ def rules(tmp_path_factory):
     L = ctypes.CDLL(so)
     L.rule_store.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int, ctypes.c_int, ctypes.c_int]
     L.rule_rec.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int]
+    L.rule_grad_rec.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_long]
     L.rule_proj_lds.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int, ctypes.c_int]
     return L
 
@@ -105,3 +106,16 @@ SPLIT = 2000
     (COMPLEX, 0, 24, 30000, 1, 4, ONE), (COMPLEX, 0, 20, 80001, 0, 4, WIDE + 54), (COMPLEX, 0, 9, 131_073, 0, 4, ONE)])
 def test_recurrence_shapes(rules, kind, f64, lmax, n, lines, unroll, shape):
     assert rules.rule_rec(kind, f64, lmax, n, lines) == 10000 * unroll + shape
+
+
+@pytest.mark.parametrize("f64,lmax,n,ppl,split,unroll", [
+    (1, 16, 65535, 1, 1, 8), (0, 1, 65535, 1, 1, 8), (1, 16, 65536, 2, 1, 2), (1, 1, 262143, 2, 1, 2),
+    # FP64 whole: a point and a degree at a time for few rows, else two points once one leaves no lane idle
+    (1, 0, 1_500_001, 1, 0, 1), (1, 1, 400_001, 1, 0, 1), (1, 3, 4_000_001, 1, 0, 1), (1, 7, 262_144, 1, 0, 1),
+    (1, 8, 262_144, 1, 0, 2), (1, 9, 327_679, 1, 0, 2), (1, 9, 327_680, 2, 0, 1), (1, 16, 400_001, 2, 0, 1),
+    (1, 10, 2_000_001, 2, 0, 1),
+    # FP32: whole earlier, and one point, for few rows
+    (0, 0, 524_287, 2, 1, 2), (0, 0, 700_001, 1, 0, 2), (0, 1, 1_048_576, 1, 0, 2), (0, 3, 4_000_001, 1, 0, 2),
+    (0, 4, 1_048_575, 2, 1, 2), (0, 4, 1_048_576, 4, 0, 2), (0, 16, 800_001, 2, 1, 2), (0, 16, 2_000_001, 4, 0, 2)])
+def test_recurrence_backward_shapes(rules, f64, lmax, n, ppl, split, unroll):
+    assert rules.rule_grad_rec(f64, lmax, n) == 10000 * unroll + 2000 * split + ppl

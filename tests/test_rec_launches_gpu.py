@@ -81,3 +81,17 @@ def test_complex_launches_agree(dev, dtype, n):
     for i in range(0, n, 50001):
         p = sh.sh_eval_complex_rec(lmax, x[i:i + 50001].contiguous())
         assert torch.equal(torch.view_as_real(y[:, i:i + 50001]), torch.view_as_real(p))
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("n,lmax", [((1 << 18) + 1, 0), ((1 << 18) + 1, 7), ((1 << 18) + 1, 8), ((5 << 16) - 1, 9),
+                                    ((5 << 16) + 1, 9), ((1 << 19) - 1, 3), ((1 << 19) + 1, 3), ((1 << 20) + 1, 0),
+                                    ((1 << 20) + 1, 1), ((1 << 20) + 3, 4)])
+def test_backward_launches_agree(dev, dtype, n, lmax):
+    """The backward's launches of one lane per point or points, whose reads of the rows of m = 0 differ."""
+    print("case: recurrence backward launches, n", n, "lmax", lmax, dtype, flush=True)
+    x, G = _inputs(n, lmax, dtype, dev)
+    _, bwd = _fns(dtype)
+    g = bwd(lmax, x, G)
+    for i in range(0, n, 65535):
+        assert torch.equal(g[i:i + 65535], bwd(lmax, x[i:i + 65535].contiguous(), G[:, i:i + 65535].contiguous()))
