@@ -117,6 +117,37 @@ inline StoreShape store_shape(int64_t n, int value, int in_bytes, bool lines)
                                                                                                       : kCapLds2};
 }
 
+// How the explicit backward kernel reads G and orders its workgroups (one point per lane: two,
+// or four in FP32, are equal or up to 25% slower below 400 MB of G and within 5% above).
+//  kCached   small: loads that keep lines, XCD-contiguous order, no cap.  G, which a caller has
+//            usually just written, is then in the memory-side cache, with what else a step
+//            touches.  us for a forward call, G = 2 y and the backward call, against kStream,
+//            FP64: lmax 9, 100 MB of G 62.7 / 63.6, 130 MB 82.5 / 87.6, 160 MB 114.7 / 110.2,
+//            195 MB 144 / 131; lmax 3, 133 MB 101 / 94; lmax 2, 92 MB 67.5 / 69.1, 133 MB 119 / 103;
+//            lmax 1, 85 MB 79.2 / 81.2, 105 MB 106 / 100; lmax 0, 60 MB 103 / 99; FP32 lmax 2, 125 MB
+//            93.8 / 98.4, lmax 1, 195 MB 194 / 222.  (One G read over and over, and little else, is
+//            15-25% faster as kCached up to 190 MB.)
+//  kStream   larger: non-temporal loads, plain order, at most 4 resident workgroups per CU.
+//            us, rows on 128-byte lines, FP64 lmax 6, 2000000 147 against 158 with loads that
+//            keep lines and 167 as kCached; FP32 145 / 156 / 167
+//  kShared   from kGradSharedBytes and lmax 3, rows off the lines: as kStream with loads that keep
+//            lines, as neighbouring waves read parts of the same ones.  FP64 lmax 6, 4194301 331
+//            against 364 streaming, lmax 8, 2000001 250 / 260; FP32 lmax 8, 4000001 247 /
+//            270; but FP64 lmax 2, 8000001 153 / 149, lmax 5, 1000001 (288 MB) 61 / 58
+enum class GRead { kCached, kStream, kShared };
+constexpr int64_t kGradSharedBytes = int64_t(1) << 29;
+
+template <int LMAX, typename TIO>
+inline GRead grad_read(int64_t n, bool lines)
+{
+    constexpr int64_t f64_lines[] = {int64_t(3) << 24, int64_t(11) << 23, int64_t(3) << 25, int64_t(15) << 23};
+    constexpr int64_t f32_lines[] = {int64_t(3) << 26, int64_t(3) << 26, int64_t(15) << 23, int64_t(15) << 23};
+    constexpr int64_t cached = LMAX >= 4 ? int64_t(1) << 27 : (sizeof(TIO) == 8 ? f64_lines : f32_lines)[LMAX];
+    const int64_t bytes = n * nfun(LMAX) * int64_t(sizeof(TIO));
+    if (bytes < cached) return GRead::kCached;
+    return LMAX >= 3 && bytes >= kGradSharedBytes && !lines ? GRead::kShared : GRead::kStream;
+}
+
 // First point of lane `t` of a launch whose lanes take PPL adjacent points of n >= PPL
 // (t * PPL < n): where PPL does not divide n the last lane takes the last PPL points,
 // some of which the lane before it takes too, and both store the same bits.

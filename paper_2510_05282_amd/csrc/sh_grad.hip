@@ -27,23 +27,6 @@ namespace shk {
 constexpr int kGradBlock = 256;
 constexpr int64_t kGradChunk = int64_t(1) << 28;
 
-// How the reads of G are made and ordered (us, at the bytes of G; plain workgroup order and
-// at most 4 resident workgroups per CU unless said otherwise; one point per lane: two, or
-// four in FP32, are equal or up to 25% slower below 400 MB and within 5% above).
-//  kCached   below kReadCachedBytes, where G, which a caller has usually just written, is
-//            in the memory-side cache: loads that keep lines, XCD-contiguous order, no cap.
-//            FP64 lmax 4, 500001 points (100 MB) 18.0 against 22.7 streaming, lmax 9, 100001
-//            13.4 / 17.5; FP32 lmax 6, 400000 13.5 / 16.2
-//  kStream   larger: non-temporal loads.  Rows on 128-byte lines, FP64 lmax 6,
-//            2000000 147 against 158 with loads that keep lines and 167 as kCached; FP32
-//            145 / 156 / 167
-//  kShared   from kGradSharedBytes and lmax 3, rows off the lines: loads that keep lines,
-//            as neighbouring waves read parts of the same ones.  FP64 lmax 6, 4194301 331
-//            against 364 streaming, lmax 8, 2000001 250 / 260; FP32 lmax 8, 4000001 247 /
-//            270; but FP64 lmax 2, 8000001 153 / 149, lmax 5, 1000001 (288 MB) 61 / 58
-enum class GRead { kCached, kStream, kShared };
-constexpr int64_t kGradSharedBytes = int64_t(1) << 29;
-
 // TIO is the element type of xyz, G and the result; the normalisation and 1/r
 // run in FP64, the polynomials and the contraction in TIO.
 template <int LMAX, typename TIO, GRead READ>
@@ -90,12 +73,13 @@ static hipError_t launch_grad_one(int64_t n, const TIO* xyz, const TIO* G, int64
 template <int LMAX, typename TIO>
 static hipError_t launch_grad_l(int64_t n, const TIO* xyz, const TIO* G, int64_t ldg, TIO* gxyz, hipStream_t s)
 {
-    const int64_t bytes = n * nfun(LMAX) * int64_t(sizeof(TIO));
-    if (bytes < kReadCachedBytes) return launch_grad_one<LMAX, TIO, GRead::kCached>(n, xyz, G, ldg, gxyz, s);
-    if constexpr (LMAX >= 3)
-        if (bytes >= kGradSharedBytes && !on_lines(G, ldg * sizeof(TIO)))
-            return launch_grad_one<LMAX, TIO, GRead::kShared>(n, xyz, G, ldg, gxyz, s);
-    return launch_grad_one<LMAX, TIO, GRead::kStream>(n, xyz, G, ldg, gxyz, s);
+    switch (grad_read<LMAX, TIO>(n, on_lines(G, ldg * sizeof(TIO)))) {
+    case GRead::kCached: return launch_grad_one<LMAX, TIO, GRead::kCached>(n, xyz, G, ldg, gxyz, s);
+    case GRead::kShared:
+        if constexpr (LMAX >= 3) return launch_grad_one<LMAX, TIO, GRead::kShared>(n, xyz, G, ldg, gxyz, s);
+        [[fallthrough]];
+    default: return launch_grad_one<LMAX, TIO, GRead::kStream>(n, xyz, G, ldg, gxyz, s);
+    }
 }
 
 template <typename TIO>

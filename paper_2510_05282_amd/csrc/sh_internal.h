@@ -27,9 +27,8 @@ template <typename TIO>
 hipError_t launch_fwd_complex(int lmax, int64_t n, int input, const TIO* in0, const TIO* in1, TIO* out, int64_t ld,
                               hipStream_t s);
 
-// The backward passes read G with loads that keep lines below this size, which the
-// memory-side cache (256 MB) holds with what else a step touches, and with non-temporal
-// loads from there on (sh_grad.hip, sh_rec.hip).
+// The recurrence's backward pass reads G with loads that keep lines below this size, which
+// the memory-side cache (256 MB) holds, and with non-temporal loads from there on.
 constexpr int64_t kReadCachedBytes = int64_t(3) << 26;
 
 // Vector-Jacobian product: gxyz[n][3] = sum_f G[f][i] dR_f/dx at xyz[n][3]; G is [F][ldg].

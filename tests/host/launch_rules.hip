@@ -73,6 +73,25 @@ static int rec_of(int kind, int lmax, int64_t n, int lines)
                      : rec(shk::rec_cplx_shape<TIO, true>(n, 8 * b, lines));
 }
 
+// 0: loads that keep lines, 1: non-temporal, 2: kept off the lines.
+template <typename TIO>
+static int grad_read_of(int lmax, int64_t n, int lines)
+{
+    switch (lmax) {
+    case 0: return int(shk::grad_read<0, TIO>(n, lines));
+    case 1: return int(shk::grad_read<1, TIO>(n, lines));
+    case 2: return int(shk::grad_read<2, TIO>(n, lines));
+    case 3: return int(shk::grad_read<3, TIO>(n, lines));
+    case 4: return int(shk::grad_read<4, TIO>(n, lines));
+    default: return int(shk::grad_read<9, TIO>(n, lines));
+    }
+}
+
+extern "C" int rule_grad_read(int f64, int lmax, long n, int lines)
+{
+    return f64 ? grad_read_of<double>(lmax, n, lines) : grad_read_of<float>(lmax, n, lines);
+}
+
 // Points per lane, plus 2000 where the m are split, and 10000 times the degrees at a time.
 extern "C" int rule_grad_rec(int f64, int lmax, long n)
 {

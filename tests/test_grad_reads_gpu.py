@@ -37,3 +37,13 @@ def test_reads_agree(dev, dtype, lmax, size, more):
     m = n // 5 + 3
     for i in range(0, n, m):
         assert torch.equal(out[i:i + m], fn(lmax, x[i:i + m].contiguous(), G[:, i:i + m].contiguous()))
+
+
+@pytest.mark.parametrize("dtype,lmax,size", [(torch.float64, 0, 3 << 24), (torch.float64, 1, 11 << 23),
+                                             (torch.float64, 2, 3 << 25), (torch.float32, 2, 15 << 23),
+                                             (torch.float64, 3, 15 << 23), (torch.float64, 4, 1 << 27),
+                                             (torch.float32, 9, 1 << 27)])
+@pytest.mark.parametrize("more", [-1, 0, 1])
+def test_reads_agree_by_lmax(dev, dtype, lmax, size, more):
+    """Around the sizes from which G is read past the caches."""
+    test_reads_agree(dev, dtype, lmax, size, more)

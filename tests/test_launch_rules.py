@@ -25,6 +25,7 @@ def rules(tmp_path_factory):
     L = ctypes.CDLL(so)
     L.rule_store.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int, ctypes.c_int, ctypes.c_int]
     L.rule_rec.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int]
+    L.rule_grad_read.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int]
     L.rule_grad_rec.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_long]
     L.rule_proj_lds.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int, ctypes.c_int]
     return L
@@ -119,3 +120,20 @@ def test_recurrence_shapes(rules, kind, f64, lmax, n, lines, unroll, shape):
     (0, 4, 1_048_575, 2, 1, 2), (0, 4, 1_048_576, 4, 0, 2), (0, 16, 800_001, 2, 1, 2), (0, 16, 2_000_001, 4, 0, 2)])
 def test_recurrence_backward_shapes(rules, f64, lmax, n, ppl, split, unroll):
     assert rules.rule_grad_rec(f64, lmax, n) == 10000 * unroll + 2000 * split + ppl
+
+
+CACHED, STREAM, SHARED = 0, 1, 2
+
+
+@pytest.mark.parametrize("f64,lmax,mb,lines,read", [
+    # MB of G; beyond these a step's other data push it out of the memory-side cache
+    (1, 9, 130, 1, CACHED), (1, 9, 160, 1, STREAM), (1, 9, 195, 0, STREAM), (0, 9, 130, 0, CACHED),
+    (0, 3, 160, 1, STREAM), (1, 3, 195, 1, STREAM), (1, 2, 100, 1, CACHED), (1, 2, 130, 1, STREAM),
+    (0, 2, 160, 0, STREAM), (1, 1, 80, 1, CACHED), (1, 1, 100, 1, STREAM), (1, 0, 60, 1, STREAM), (1, 0, 50, 1, CACHED),
+    (1, 3, 125, 1, CACHED), (0, 3, 133, 1, STREAM), (0, 2, 125, 1, CACHED), (0, 4, 133, 0, CACHED),
+    (0, 1, 195, 1, CACHED), (0, 0, 195, 1, CACHED), (0, 1, 210, 1, STREAM),
+    (1, 9, 530, 0, STREAM), (1, 9, 540, 0, SHARED), (1, 9, 540, 1, STREAM), (0, 3, 900, 0, SHARED),
+    (1, 2, 900, 0, STREAM)])
+def test_backward_reads(rules, f64, lmax, mb, lines, read):
+    n = mb * 10**6 // ((lmax + 1) ** 2 * (8 if f64 else 4))
+    assert rules.rule_grad_read(f64, lmax, n, lines) == read
