@@ -45,8 +45,9 @@ def row(l: int, m: int) -> int:
 # What a call needs from torch besides its tensors: the stream's handle, and its device
 # to be the current one.  The handle comes as a number (building a Stream object takes 2-3
 # us of host time, a small call's launch 4), and the device is set only where it differs.
-_raw_stream = torch._C._cuda_getCurrentRawStream
-_current_device = torch._C._cuda_getDevice
+# A torch built without GPU support has neither name, nor tensors that get this far.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream(dev: torch.device, stream) -> int:

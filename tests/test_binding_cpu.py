@@ -1,6 +1,10 @@
 """The Python binding without a GPU: errors of the runtime calls that it makes itself."""
 from __future__ import annotations
 
+import os
+import subprocess
+import sys
+
 import pytest
 
 from paper_2510_05282_amd import serve
@@ -41,3 +45,22 @@ def test_release_reports_the_failing_synchronisation(monkeypatch):
     s.release(t)
     assert s.poll(t) == serve.RELEASED
     s.close()
+
+
+def test_import_without_gpu_support():
+    """A torch built for the CPU alone: the package imports, its host parts run, and a call on a
+    CPU tensor is refused as it is with any torch."""
+    code = """
+import torch
+for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+    delattr(torch._C, name)
+import paper_2510_05282_amd as sh
+assert sh.row(3, -2) == 10
+try:
+    sh.sh_eval(2, torch.randn(5, 3, dtype=torch.float64))
+except (TypeError, ValueError) as e:
+    print("refused", type(e).__name__)
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "refused" in r.stdout, r.stderr
