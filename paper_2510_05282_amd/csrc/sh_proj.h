@@ -24,9 +24,9 @@ struct SplineGrid {
 // R_0 .. R_{NL-1} at r >= 0 from a table with ch >= NL channels: interval
 // i = floor(r/h) clamped to [0, n_r-2], t = r/h - i, A = 1 - t, B = t,
 //     S = A y_i + B y_{i+1} + ((A^3 - A) M_i + (B^3 - B) M_{i+1}) h^2/6;
-// 0 beyond r_max; a NaN r gives NaN.  Split in two steps: spline_knots loads
-// the pairs of knots i and i+1 (for any r: beyond r_max or NaN it reads interval 0,
-// which spline_from then ignores), spline_from evaluates the cubic from them.
+// 0 beyond r_max; a NaN r gives NaN.  spline_eval, below, is the one to call; its steps:
+// spline_knots loads the pairs of knots i and i+1 (r <= r_max), spline_from evaluates the
+// cubic from them (any r; the pairs are not used beyond r_max or for NaN).
 __host__ __device__ __forceinline__ int spline_interval(double r, const SplineGrid& g)
 {
     const double q = r <= g.r_max ? r * g.inv_h : 0.0;
@@ -87,7 +87,7 @@ __host__ __device__ __forceinline__ void spline_from(const float2 (&a)[NL], cons
     });
 }
 
-// Both steps for one point, with the loads skipped beyond r_max.
+// Both steps for one point; nothing is loaded beyond r_max.
 template <int NL, typename TIO, typename KN>
 __host__ __device__ __forceinline__ void spline_eval(const KN* __restrict__ tab, int ch, const SplineGrid& g,
                                                      double r, TIO (&R)[NL])

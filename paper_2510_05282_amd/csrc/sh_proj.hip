@@ -15,7 +15,7 @@
 // Launch: workgroups remapped so each XCD works through one contiguous range of atoms
 // (their tables then stay in that XCD's L2); the atom of a wave found by one wave-wide
 // search or from a preload; plain stores; one point per lane, or several in large builds,
-// some of which hold the atom's table in LDS (proj_launch).
+// some of which hold the atom's table in LDS (launch_proj_l).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
