@@ -578,9 +578,9 @@ static hipError_t launch_proj_lds(const ProjArgs<TIO>& A, const SplineGrid& g, h
         const int64_t n_groups = wgs >> group_log, load_cost = kProjLoadCost + proj_lds_bytes<TIO, LMAX>(A.n_r) / 256;
         const int64_t group_cost = (A.n_points + A.n_atoms * load_cost + n_groups - 1) / n_groups;
         hipLaunchKernelGGL((proj_lds_kernel<LMAX, TIO, P, BT>), dim3(wgs), dim3(BT),
-                           std::max(size_t(proj_lds_bytes<TIO, LMAX>(A.n_r)), sizeof(ProjShare)), s, A.centers, A.offsets, A.n_atoms, A.points,
-                           A.n_points, A.table, A.n_tables, A.table_of_atom, g, A.out, group_cost, group_log,
-                           int(load_cost));
+                           std::max(size_t(proj_lds_bytes<TIO, LMAX>(A.n_r)), sizeof(ProjShare)), s, A.centers,
+                           A.offsets, A.n_atoms, A.points, A.n_points, A.table, A.n_tables, A.table_of_atom, g, A.out,
+                           group_cost, group_log, int(load_cost));
         return hipGetLastError();
     } else {
         return hipErrorInvalidValue;
