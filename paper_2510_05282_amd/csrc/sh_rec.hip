@@ -104,8 +104,11 @@ template hipError_t launch_rec<float>(int, int64_t, const float*, float*, int64_
 // took 124 us in FP64 (3.8 TB/s) and 110 in FP32 (2.1), 10001 points 84 and 75; now 81
 // (5.8 TB/s), 47 (5.0), 11 and 10.  grad_rec_shape says which launch.  FP32's split launches are
 // held to 72 registers, seven waves a SIMD: 400001 points at lmax 9 26.3 us, 28.6 at six waves.
+template <typename TIO, bool SPLIT>
+constexpr int kGradRecWaves = sizeof(TIO) == 8 ? (SPLIT ? 1 : 4) : (SPLIT ? 7 : 1);  // a SIMD, at least
+
 template <typename TIO, int PPL, bool SPLIT, int UNROLL, bool NT>
-__global__ __launch_bounds__(kRecBlock, !SPLIT && sizeof(TIO) == 8 ? 4 : SPLIT && sizeof(TIO) == 4 ? 7 : 1) void grad_rec_kernel(
+__global__ __launch_bounds__(kRecBlock, (kGradRecWaves<TIO, SPLIT>)) void grad_rec_kernel(
     const TIO* __restrict__ xyz, const TIO* __restrict__ G, TIO* __restrict__ gxyz, uint32_t n, int64_t ldg, int lmax)
 {
     using V = typename vec_of<TIO, PPL>::type;
